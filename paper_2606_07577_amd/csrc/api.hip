@@ -507,7 +507,6 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
       (e = dalloc(ctx, &ws.lse2, L * Hq * Cm)) != hipSuccess ||
       (e = dalloc(ctx, &ws.part, L * Hq * (size_t)dm.kb * kMaxSeg * kScoreBlock)) != hipSuccess ||
       (e = dalloc(ctx, &ws.pos, L * 2 * (size_t)list_stride(T))) != hipSuccess ||
-      (e = dalloc(ctx, &ws.rank, L * T)) != hipSuccess ||
       (e = dalloc(ctx, &ws.counts, L * 2)) != hipSuccess ||
       (e = dalloc(ctx, &ws.inv_norm, L * Hkv * T)) != hipSuccess ||
       (e = dalloc(ctx, &ws.best, L * Hkv * T)) != hipSuccess ||

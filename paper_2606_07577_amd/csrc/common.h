@@ -260,7 +260,6 @@ struct Workspace {
   float* lse2;            // [L][Hq][max_chunk] merged normaliser, log2 units
   float* part;            // [L][Hq][kb][kMaxSeg][256] partial column sums per query head
   int* pos;               // [L][2][max_tokens + kListPad] visual rows, audio rows (ascending)
-  int* rank;              // [L][max_tokens]  rank of row j inside its modality
   int* counts;            // [L][2]           K_v, K_a
   float* inv_norm;        // [L][Hkv][max_tokens] inverse norms, segment order
   int* best;              // [L][Hkv][max_tokens] ord_f32 of the best cosine, segment order

@@ -22,14 +22,12 @@ namespace {
 
 // --- modality lists --------------------------------------------------------
 // Per layer: pos[l][0][0 .. K_v) = visual rows ascending, pos[l][1][0 .. K_a)
-// = audio rows ascending; rank[j] = index of row j inside its modality's
-// list.  One workgroup per layer: a counting pass, one scan of the wave
+// = audio rows ascending.  One workgroup per layer: a counting pass, one scan of the wave
 // counts, and a placing pass.
 
 
 __global__ __launch_bounds__(1024) void modality_lists(const LayerDesc* __restrict__ layers, Dims dm,
-                                                      int* __restrict__ pos, int* __restrict__ rank,
-                                                      int* __restrict__ counts) {
+                                                      int* __restrict__ pos, int* __restrict__ counts) {
   const int l = blockIdx.x;
   const int N = layers[l].n;
   const uint8_t* mod = layers[l].mod;
@@ -38,7 +36,6 @@ __global__ __launch_bounds__(1024) void modality_lists(const LayerDesc* __restri
   const unsigned long long lt = (1ull << lane) - 1ull;
   int* Pv = pos + (int64_t)(2 * l) * list_stride(dm.max_tokens);
   int* Pa = Pv + list_stride(dm.max_tokens);
-  int* R = rank + (int64_t)l * dm.max_tokens;
   // Wave w owns rows [w * 64S, (w + 1) * 64S); step i covers the 64
   // consecutive rows w * 64S + 64 i + lane, so reads and writes coalesce.
   const int S = (N + (int)blockDim.x - 1) / (int)blockDim.x;
@@ -76,8 +73,8 @@ __global__ __launch_bounds__(1024) void modality_lists(const LayerDesc* __restri
       const int j = wrow0 + (i0 + u) * 64 + lane;
       const unsigned long long bal = __ballot(vis[u]);
       const int rv = run + __popcll(bal & lt);  // visual rows before j
-      if (vis[u]) { Pv[rv] = j; R[j] = rv; }
-      else if (i0 + u < S && j < N) { Pa[j - rv] = j; R[j] = j - rv; }
+      if (vis[u]) Pv[rv] = j;
+      else if (i0 + u < S && j < N) Pa[j - rv] = j;
       run += __popcll(bal);
     }
   }
@@ -112,14 +109,13 @@ struct GatherShape {
 // head), counts the visual rows of the whole layer and those
 // before j0 from the modality mask itself, places its rows by a ballot
 // prefix, and copies them to their segment positions with their inverse
-// norms.  The workgroups of KV head 0 also write the lists (pos, rank,
+// norms.  The workgroups of KV head 0 also write the lists (pos,
 // counts) for the later kernels.
 constexpr int kListRows = 128;
 
 template <typename T, int D, bool PERM>
 __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__ layers, Dims dm, int on_keys,
-                                                   int* __restrict__ pos, int* __restrict__ rank,
-                                                   int* __restrict__ counts, T* __restrict__ perm,
+                                                   int* __restrict__ pos, int* __restrict__ counts, T* __restrict__ perm,
                                                    float* __restrict__ inv, int* __restrict__ best) {
   const int l = blockIdx.z, g = blockIdx.y;
   const LayerDesc Ld = layers[l];
@@ -201,7 +197,6 @@ __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__
         dst[q * 64 + lane] = vis ? r : kv + r;
         if (g == 0) {
           pos[(int64_t)(2 * l + (vis ? 0 : 1)) * list_stride(dm.max_tokens) + r] = j;
-          rank[(int64_t)l * dm.max_tokens + j] = r;
         }
         if (r == (vis ? kv : N - kv) - 1) last[vis ? 0 : 1] = j;
       }
@@ -477,48 +472,9 @@ __global__ void gram_finish(const LayerDesc* __restrict__ layers, Dims dm, const
 }
 
 // --- SIM_ADJ: Eq. (7) with the modality's own neighbours --------------------
-template <typename T, int D>
-__device__ double cos64(const T* x, const T* y) {
-  double xy = 0.0, xx = 0.0, yy = 0.0;
-  for (int e = 0; e < D; ++e) {
-    double a, b;
-    if constexpr (sizeof(T) == 2) { a = __uint_as_float(((uint32_t)x[e]) << 16); b = __uint_as_float(((uint32_t)y[e]) << 16); }
-    else { a = x[e]; b = y[e]; }
-    xy += a * b; xx += a * a; yy += b * b;
-  }
-  if (xx <= 0.0 || yy <= 0.0) return 0.0;
-  const double c = xy / (sqrt(xx) * sqrt(yy));
-  return c > 1.0 ? 1.0 : (c < -1.0 ? -1.0 : c);
-}
-
-template <typename T, int D>
-__global__ void adjacent_cos(const LayerDesc* __restrict__ layers, Dims dm, int on_keys, const int* __restrict__ pos,
-                             const int* __restrict__ rank, const int* __restrict__ counts, float* __restrict__ s) {
-  const int l = blockIdx.z, g = blockIdx.y;
-  const LayerDesc Ld = layers[l];
-  const int N = Ld.n;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
-  const int mu = Ld.mod[j] ? 1 : 0;
-  const int K = counts[2 * l + mu];
-  const int* P = pos + (int64_t)(2 * l + mu) * list_stride(dm.max_tokens);
-  const int t = rank[(int64_t)l * dm.max_tokens + j];
-  const T* u = reinterpret_cast<const T*>(on_keys ? Ld.k : Ld.v) + (int64_t)g * Ld.kv_hs;
-  const T* x = u + (int64_t)j * Ld.kv_rs;
-  double sum = 0.0;
-  int n = 0;
-  if (t > 0) { sum += cos64<T, D>(x, u + (int64_t)P[t - 1] * Ld.kv_rs); ++n; }
-  if (t + 1 < K) { sum += cos64<T, D>(x, u + (int64_t)P[t + 1] * Ld.kv_rs); ++n; }
-  s[((int64_t)l * dm.Hkv + g) * dm.max_tokens + j] = n ? (float)(sum / n) : 0.0f;
-}
-
-// --- Eq. (7) as printed: on the layer's hidden states ------------------------
-// One wave per working-set row j: the cosines of hidden state j with the
-// previous and the next row of its modality (fp64 sums over the 16-byte
-// pieces of the rows, lanes strided, then across the wave), their mean
-// written to every KV head's row of s: hidden states are per token.
+// One 16-byte piece of a row as fp64 values.
 template <typename T>
-__device__ inline void add_piece(const uint4& p, float (&out)[16 / sizeof(T)]) {
+__device__ inline void piece_f64(const uint4& p, double (&out)[16 / sizeof(T)]) {
   const uint32_t w[4] = {p.x, p.y, p.z, p.w};
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -531,58 +487,113 @@ __device__ inline void add_piece(const uint4& p, float (&out)[16 / sizeof(T)]) {
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void adjacent_cos_hidden(const LayerDesc* __restrict__ layers, Dims dm,
-                                                           const int* __restrict__ pos, const int* __restrict__ rank,
-                                                           const int* __restrict__ counts, float* __restrict__ s) {
-  const int l = blockIdx.y;
-  const LayerDesc Ld = layers[l];
-  const int N = Ld.n;
-  const int lane = threadIdx.x & 63;
-  const int j = (int)blockIdx.x * 4 + wave_id();
-  if (j >= N) return;  // the whole wave leaves
-  const int mu = Ld.mod[j] ? 1 : 0;
-  const int K = counts[2 * l + mu];
-  const int* P = pos + (int64_t)(2 * l + mu) * list_stride(dm.max_tokens);
-  const int t = rank[(int64_t)l * dm.max_tokens + j];
-  const int jp = t > 0 ? P[t - 1] : -1, jn = t + 1 < K ? P[t + 1] : -1;
-  const T* H = reinterpret_cast<const T*>(Ld.hidden);
-  const T* x = H + (int64_t)j * Ld.hidden_rs;
-  const T* xp = H + (int64_t)(jp < 0 ? j : jp) * Ld.hidden_rs;
-  const T* xn = H + (int64_t)(jn < 0 ? j : jn) * Ld.hidden_rs;
-  constexpr int EPP = 16 / (int)sizeof(T);  // elements per 16-byte piece
-  const int pieces = dm.dh / EPP;
-  double xx = 0.0, pp = 0.0, nn = 0.0, xpd = 0.0, xnd = 0.0;
-  for (int c = lane; c < pieces; c += 64) {
-    float a[EPP], b[EPP], d[EPP];
-    add_piece<T>(gload16(x + c * EPP), a);
-    add_piece<T>(gload16(xp + c * EPP), b);
-    add_piece<T>(gload16(xn + c * EPP), d);
+// The mean cosine of each row with the previous and the next row of its
+// modality, on keys, values or (HIDDEN) hidden states, whose value goes to
+// every KV head's row of s: hidden states are per token.  LPR lanes hold one
+// 16-byte piece each of a row (or every LPR-th piece of a longer one) and
+// take R consecutive positions of the modality lists (visual rows, then
+// audio rows) at a time: R + 2 rows are read, each once, for R rows' two
+// cosines, all requested before the first sum.  Sums in fp64, across the
+// lanes at the end; lane i of the group then holds cosine i (positions
+// p0 + i - 1 and p0 + i), so each lane takes one square root and division.
+// Bound by HBM (the rows once, plus the two rows at the ends of a group from
+// L2).  One thread per row reading its three rows element by element took
+// 218 us on 28 layers of 6144 bf16 rows x 4 heads of 128 (0.8 TB/s); this
+// takes
+// 44.5 us (4.0 TB/s); 4 rows a group 51, 12 rows 44.0, 14 rows (176 registers) 52.
+template <int LPR> constexpr int adj_rows() { return LPR < 16 ? 6 : 8; }
+
+template <typename T, int LPR, bool HIDDEN>
+__global__ __launch_bounds__(256) void adjacent_cos(const LayerDesc* __restrict__ layers, Dims dm, int on_keys,
+                                                    const int* __restrict__ pos, const int* __restrict__ counts,
+                                                    float* __restrict__ s) {
+  constexpr int R = adj_rows<LPR>(), V = R + 2, EPP = 16 / (int)sizeof(T);
+  static_assert(V <= LPR, "a lane of the group for every row's sum");
+  const int l = blockIdx.z, g = blockIdx.y;
+  const LayerDesc& Ld = layers[l];
+  const int N = Ld.n, kv = counts[2 * l];
+  const int lane = threadIdx.x & 63, sub = lane % LPR;
+  const int p0 = (int)((blockIdx.x * 256 + threadIdx.x) / LPR) * R;
+  if (p0 >= N) return;  // the lanes of the group leave together
+  const int* P = pos + (int64_t)(2 * l) * list_stride(dm.max_tokens);
+  const int64_t audio = list_stride(dm.max_tokens) - kv;  // list entry of position p >= kv: p + audio
+  int row[V];
 #pragma unroll
-    for (int e = 0; e < EPP; ++e) {
-      const double u = a[e], v = b[e], w = d[e];
-      xx += u * u; pp += v * v; nn += w * w; xpd += u * v; xnd += u * w;
+  for (int i = 0; i < V; ++i) {
+    const int p = min(max(p0 - 1 + i, 0), N - 1);
+    row[i] = gload<int>(P + (p < kv ? (int64_t)p : p + audio));
+  }
+  const T* u = reinterpret_cast<const T*>(HIDDEN ? Ld.hidden : on_keys ? Ld.k : Ld.v) + (HIDDEN ? 0 : (int64_t)g * Ld.kv_hs);
+  const int64_t rs = HIDDEN ? Ld.hidden_rs : Ld.kv_rs;
+  const int pieces = HIDDEN ? dm.dh / EPP : LPR;
+  double nn[V] = {}, xy[R + 1] = {};
+  for (int c = sub; c < pieces; c += LPR) {
+    uint4 v[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] = gload16(u + (int64_t)row[i] * rs + c * EPP);
+    double x[EPP], y[EPP];
+    piece_f64<T>(v[0], x);
+#pragma unroll
+    for (int e = 0; e < EPP; ++e) nn[0] += x[e] * x[e];
+#pragma unroll
+    for (int i = 1; i < V; ++i) {
+      piece_f64<T>(v[i], y);
+#pragma unroll
+      for (int e = 0; e < EPP; ++e) {
+        nn[i] += y[e] * y[e];
+        xy[i - 1] += x[e] * y[e];
+        x[e] = y[e];
+      }
     }
   }
+  // lane i of the group: row i's squared norm and row i's product with row i + 1
+  double my_nn = 0.0, my_xy = 0.0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    xx += __shfl_xor(xx, o, 64);
-    pp += __shfl_xor(pp, o, 64);
-    nn += __shfl_xor(nn, o, 64);
-    xpd += __shfl_xor(xpd, o, 64);
-    xnd += __shfl_xor(xnd, o, 64);
+  for (int i = 0; i < V; ++i) {
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) {
+      nn[i] += __shfl_xor(nn[i], o, 64);
+      if (i <= R) xy[min(i, R)] += __shfl_xor(xy[min(i, R)], o, 64);
+    }
+    my_nn = sub == i ? nn[i] : my_nn;
+    if (i <= R) my_xy = sub == i ? xy[min(i, R)] : my_xy;
   }
-  auto cosv = [](double xy, double aa, double bb) {
-    if (aa <= 0.0 || bb <= 0.0) return 0.0;
-    const double c = xy / (sqrt(aa) * sqrt(bb));
-    return c > 1.0 ? 1.0 : (c < -1.0 ? -1.0 : c);
-  };
-  double sum = 0.0;
-  int n = 0;
-  if (jp >= 0) { sum += cosv(xpd, xx, pp); ++n; }
-  if (jn >= 0) { sum += cosv(xnd, xx, nn); ++n; }
-  const float v = n ? (float)(sum / n) : 0.0f;
-  for (int g = lane; g < dm.Hkv; g += 64) s[((int64_t)l * dm.Hkv + g) * dm.max_tokens + j] = v;
+  int my_row = 0;  // of position p0 + sub
+#pragma unroll
+  for (int i = 0; i < R; ++i) my_row = sub == i ? row[i + 1] : my_row;
+  const double next_nn = __shfl(my_nn, lane + 1, 64);
+  const int p = p0 + sub;
+  const bool pair = sub <= R && p >= 1 && p < N && p != kv;  // positions p - 1 and p: one list's neighbours
+  double c = 0.0;
+  if (pair && !(my_nn <= 0.0) && !(next_nn <= 0.0)) {
+    c = my_xy / (sqrt(my_nn) * sqrt(next_nn));
+    c = c > 1.0 ? 1.0 : (c < -1.0 ? -1.0 : c);
+  }
+  const double c_next = __shfl(c, lane + 1, 64);
+  const int n = (pair ? 1 : 0) + __shfl(pair ? 1 : 0, lane + 1, 64);
+  if (sub < R && p < N) {
+    const float v = n ? (float)((c + c_next) / n) : 0.0f;
+    if constexpr (HIDDEN) {
+      for (int h = 0; h < dm.Hkv; ++h) s[((int64_t)l * dm.Hkv + h) * dm.max_tokens + my_row] = v;
+    } else {
+      s[((int64_t)l * dm.Hkv + g) * dm.max_tokens + my_row] = v;
+    }
+  }
+}
+
+// One 16-byte piece of a row as fp32 values.
+template <typename T>
+__device__ inline void add_piece(const uint4& p, float (&out)[16 / sizeof(T)]) {
+  const uint32_t w[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (sizeof(T) == 2) {
+      out[2 * e] = __uint_as_float(w[e] << 16);
+      out[2 * e + 1] = __uint_as_float(w[e] & 0xFFFF0000u);
+    } else {
+      out[e] = __uint_as_float(w[e]);
+    }
+  }
 }
 
 // --- all-pairs maximum on hidden states (Eq. 7's redundancy as the maximum
@@ -1191,7 +1202,9 @@ void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, c
                   hipStream_t st) {
   const dim3 gtok((unsigned)((dm.max_tokens + 255) / 256), dm.Hkv, dm.L);
   if (sim == 1) {
-    OMNIMEM_LAUNCH(ws, K_ADJ, st, adjacent_cos<T, D><<<gtok, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.rank, ws.counts, s));
+    constexpr int LPR = GatherShape<T, D>::LPR, kRows = 256 / LPR * adj_rows<LPR>();
+    const dim3 grid((unsigned)((dm.max_tokens + kRows - 1) / kRows), dm.Hkv, dm.L);
+    OMNIMEM_LAUNCH(ws, K_ADJ, st, adjacent_cos<T, LPR, false><<<grid, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, s));
     return;
   }
   const dim3 glist((unsigned)((dm.max_tokens + kListRows - 1) / kListRows), dm.Hkv, dm.L);
@@ -1199,7 +1212,7 @@ void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, c
   const bool by_xcd = dm.L * dm.Hkv >= 2 * kXcds && ws.gram_grid % kXcds == 0;
   if constexpr (sizeof(T) == 2) {  // bf16: each pair once, rows gathered through the row lists
     OMNIMEM_LAUNCH(ws, K_NORMS, st,
-                   lists_norms<T, D, false><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.rank, ws.counts,
+                   lists_norms<T, D, false><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts,
                                                                    perm, ws.inv_norm, ws.best));
     if (by_xcd)
       OMNIMEM_LAUNCH(ws, K_GRAM_SYM, st,
@@ -1213,7 +1226,7 @@ void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, c
     return;
   }
   OMNIMEM_LAUNCH(ws, K_NORMS, st,
-                 lists_norms<T, D, true><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.rank, ws.counts, perm,
+                 lists_norms<T, D, true><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, perm,
                                                                 ws.inv_norm, ws.best));
   if (by_xcd)
     OMNIMEM_LAUNCH(ws, K_GRAM, st,
@@ -1227,7 +1240,7 @@ void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, c
 }  // namespace
 
 hipError_t launch_lists(const Dims& dm, const LayerDesc* desc, const Workspace& ws, hipStream_t st) {
-  OMNIMEM_LAUNCH(ws, K_LISTS, st, modality_lists<<<dm.L, 1024, 0, st>>>(desc, dm, ws.pos, ws.rank, ws.counts));
+  OMNIMEM_LAUNCH(ws, K_LISTS, st, modality_lists<<<dm.L, 1024, 0, st>>>(desc, dm, ws.pos, ws.counts));
   return hipGetLastError();
 }
 
@@ -1257,13 +1270,12 @@ hipError_t launch_redundancy(const Dims& dm, int dtype, int sim, int source, con
     return hipGetLastError();
   }
   if (source == 2) {  // hidden states, adjacent
-    const dim3 grid((unsigned)((dm.max_tokens + 3) / 4), dm.L);
+    constexpr int kRows = 256 / 64 * adj_rows<64>();
+    const dim3 grid((unsigned)((dm.max_tokens + kRows - 1) / kRows), 1, dm.L);
     if (dtype == 0)
-      OMNIMEM_LAUNCH(ws, K_ADJ_H, st, adjacent_cos_hidden<uint16_t><<<grid, 256, 0, st>>>(desc, dm, ws.pos, ws.rank,
-                                                                                       ws.counts, s));
+      OMNIMEM_LAUNCH(ws, K_ADJ_H, st, adjacent_cos<uint16_t, 64, true><<<grid, 256, 0, st>>>(desc, dm, 0, ws.pos, ws.counts, s));
     else
-      OMNIMEM_LAUNCH(ws, K_ADJ_H, st, adjacent_cos_hidden<float><<<grid, 256, 0, st>>>(desc, dm, ws.pos, ws.rank,
-                                                                                    ws.counts, s));
+      OMNIMEM_LAUNCH(ws, K_ADJ_H, st, adjacent_cos<float, 64, true><<<grid, 256, 0, st>>>(desc, dm, 0, ws.pos, ws.counts, s));
     return hipGetLastError();
   }
   const int on_keys = source == 1 ? 1 : 0;
