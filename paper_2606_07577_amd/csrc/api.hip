@@ -58,7 +58,7 @@ void prof_mark(Profiler* p, int kid, hipStream_t st, bool begin) {
 static const char* kKernelNames[K_COUNT] = {
     "lse_pass", "lse_merge", "colsum_pass", "head_sum", "modality_lists", "lists_norms", "gram_pass", "gram_finish", "adjacent_cos", "avba_partials", "avba_allocate", "psi_topk", "gather_compact",
     "gather_hidden", "adjacent_cos_hidden", "hidden_norms", "gram_wide", "hidden_finish", "layer_inputs",
-    "stage_moved_back", "gather_inplace", "append_chunk", "gram_sym", "topk_hist", "topk_bin", "topk_emit", "psi_topk_reg"};
+    "stage_moved_back", "gather_inplace", "append_chunk", "gram_sym", "topk_hist", "topk_bin", "topk_emit", "psi_topk_reg", "split_rows"};
 
 struct omnimem_ctx {
   omnimem_config cfg;
@@ -510,8 +510,10 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
       (e = dalloc(ctx, &ws.counts, L * 2)) != hipSuccess ||
       (e = dalloc(ctx, &ws.inv_norm, L * Hkv * T)) != hipSuccess ||
       (e = dalloc(ctx, &ws.best, L * Hkv * T)) != hipSuccess ||
-      (c.dtype != OMNIMEM_BF16 &&  // fp32 rows are copied in segment order for the Gram pass
-       (e = dalloc(ctx, reinterpret_cast<char**>(&ws.perm), L * Hkv * T * (size_t)c.head_dim * elt)) != hipSuccess) ||
+      (c.dtype != OMNIMEM_BF16 &&  // fp32 rows are split for the matrix cores; the Gram pass's in segment order
+       ((e = dalloc(ctx, &ws.perm, L * Hkv * T * 3 * (size_t)c.head_dim)) != hipSuccess ||
+        (e = dalloc(ctx, &ws.split_q, L * Hq * Cm * 3 * (size_t)c.head_dim)) != hipSuccess ||
+        (e = dalloc(ctx, &ws.split_k, L * Hkv * T * 3 * (size_t)c.head_dim)) != hipSuccess)) ||
       (e = dalloc(ctx, &ws.stat_part, L * Hkv * (size_t)allocate_part_chunks(dm) * 2 * 4)) != hipSuccess ||
       (e = dalloc(ctx, &ws.calib, L)) != hipSuccess ||
       (e = dalloc(ctx, &ws.eff, L * 2)) != hipSuccess ||

@@ -173,39 +173,6 @@ __device__ inline int xcd_swizzle(unsigned b, unsigned grid) {
 // Row of the 32x32 output tile held by accumulator register r of lane l.
 __device__ inline int acc_row(int r, int lane) { return (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); }
 
-// LDS row padding: 16 bytes keeps ds_read_b128 of consecutive rows on
-// different banks.
-template <typename T> constexpr int lds_pad() { return 16 / (int)sizeof(T); }
-
-// Copy `rows` rows of D elements from global (row r at src + r*row_stride)
-// into an LDS tile with row stride D + pad; rows at or past `valid` are
-// zero-filled.  Every thread of the block takes part.
-template <typename T, int D>
-__device__ inline void stage_rows(T* lds, const T* src, int64_t row_stride, int rows, int valid) {
-  constexpr int CPR = D * (int)sizeof(T) / 16;  // 16-byte chunks per row
-  constexpr int LD = D + lds_pad<T>();
-  for (int c = threadIdx.x; c < rows * CPR; c += blockDim.x) {
-    const int r = c / CPR, x = c % CPR;
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (r < valid) val = gload16(src + (int64_t)r * row_stride + x * (16 / sizeof(T)));
-    *reinterpret_cast<uint4*>(lds + r * LD + x * (16 / sizeof(T))) = val;
-  }
-}
-
-// Same, with an explicit row list (gathered rows).
-template <typename T, int D>
-__device__ inline void stage_rows_gather(T* lds, const T* base, int64_t row_stride, const int* rows_idx,
-                                         int rows, int valid) {
-  constexpr int CPR = D * (int)sizeof(T) / 16;
-  constexpr int LD = D + lds_pad<T>();
-  for (int c = threadIdx.x; c < rows * CPR; c += blockDim.x) {
-    const int r = c / CPR, x = c % CPR;
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (r < valid) val = gload16(base + (int64_t)rows_idx[r] * row_stride + x * (16 / sizeof(T)));
-    *reinterpret_cast<uint4*>(lds + r * LD + x * (16 / sizeof(T))) = val;
-  }
-}
-
 // Order-preserving map float -> int32 (signed compare), an involution.
 __device__ inline int ord_f32(float f) {
   int i = __float_as_int(f);
@@ -238,7 +205,7 @@ __host__ __device__ inline int64_t topk_stride(int64_t max_tokens) {
 enum KernelId {
   K_LSE, K_LSE_MERGE, K_COLSUM, K_HEADSUM, K_LISTS, K_NORMS, K_GRAM, K_GRAM_FINISH, K_ADJ,
   K_AVBA_PART, K_AVBA_ALLOC, K_TOPK, K_GATHER, K_GATHER_H, K_ADJ_H, K_NORMS_H, K_GRAM_H, K_FINISH_H, K_LAYER_IN,
-  K_STAGE, K_GATHER_IP, K_APPEND, K_GRAM_SYM, K_TOPK_HIST, K_TOPK_BIN, K_TOPK_EMIT, K_TOPK_REG, K_COUNT
+  K_STAGE, K_GATHER_IP, K_APPEND, K_GRAM_SYM, K_TOPK_HIST, K_TOPK_BIN, K_TOPK_EMIT, K_TOPK_REG, K_SPLIT, K_COUNT
 };
 struct Profiler;
 void prof_mark(Profiler* p, int kernel, hipStream_t st, bool begin);
@@ -263,7 +230,9 @@ struct Workspace {
   int* counts;            // [L][2]           K_v, K_a
   float* inv_norm;        // [L][Hkv][max_tokens] inverse norms, segment order
   int* best;              // [L][Hkv][max_tokens] ord_f32 of the best cosine, segment order
-  void* perm;             // fp32 only: [L][Hkv][max_tokens][d] rows in segment order (visual, then audio)
+  uint16_t* perm;         // fp32 only: [L][Hkv][max_tokens][3 d] split rows in segment order (visual, then audio)
+  uint16_t* split_q;      // fp32 only: [L][Hq][max_chunk][3 d] split queries (see SplitTile)
+  uint16_t* split_k;      // fp32 only: [L][Hkv][max_tokens][3 d] split keys
   int gram_grid;          // persistent Gram workgroups
   double* stat_part;      // [L][Hkv][chunks][2][4]
   double* calib;          // [L] sums of C^(l) over the calibration steps
@@ -425,7 +394,8 @@ __device__ inline void dma16_opaque(const void* g, void* lds) {
 
 // dma16_opaque with the global address split into a wave-uniform base (in
 // scalar registers) and a 32-bit per-lane byte offset, so that no 64-bit
-// address arithmetic runs per lane.
+// address arithmetic runs per lane.  (vcc is named so that the saved M0 goes
+// to a numbered register.)
 __device__ inline void dma16_opaque_s(const void* base, uint32_t off, void* lds) {
   const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane(
       (int)(uintptr_t)(__attribute__((address_space(3))) void*)lds);
@@ -438,7 +408,7 @@ __device__ inline void dma16_opaque_s(const void* base, uint32_t off, void* lds)
       "s_mov_b32 m0, %0"
       : "=&s"(saved)
       : "v"(off), "s"(base), "s"(m0)
-      : "memory");
+      : "memory", "vcc");
 }
 
 // A wave's DMA copies count as vector-memory loads; s_barrier does not wait
@@ -453,5 +423,102 @@ __device__ inline void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memor
 template <typename V>
 __device__ inline void pin(V& v) { asm volatile("" : "+v"(v)); }
 
+
+// ---------------------------------------------------------------------------
+// fp32 products on the bf16 matrix cores.  An fp32 value is the exact sum of
+// three bf16 values (its leading 8, middle 8 and last 8 significand bits, cut
+// off, not rounded), so a product of two is nine bf16 products; the three
+// below 2^-24 of the whole are left out, about what one fp32 rounding of the
+// product is worth, and the other six are added in fp32 by the MFMA.  Six
+// 32x32x16 bf16 MFMAs (32 cycles each) replace eight 32x32x2 fp32 ones (64
+// cycles each).  Rows are kept as [D leading | D middle | D last] bf16.
+// ---------------------------------------------------------------------------
+__device__ inline void split3(float x, uint32_t (&part)[3]) {
+  const uint32_t u = __float_as_uint(x);
+  part[0] = u >> 16;
+  // (infinities and NaN have no rest)
+  const float r1 = (u & 0x7F800000u) == 0x7F800000u ? 0.0f : x - __uint_as_float(u & 0xFFFF0000u);
+  const uint32_t u1 = __float_as_uint(r1);
+  part[1] = u1 >> 16;
+  part[2] = __float_as_uint(r1 - __uint_as_float(u1 & 0xFFFF0000u)) >> 16;
+}
+
+// Four fp32 elements to their places in a split row (dst: the first one's
+// leading part; the parts are D elements apart).
+__device__ inline void store_split(uint16_t* dst, int D, const uint4& v) {
+  uint32_t a[4][3];
+  split3(__uint_as_float(v.x), a[0]);
+  split3(__uint_as_float(v.y), a[1]);
+  split3(__uint_as_float(v.z), a[2]);
+  split3(__uint_as_float(v.w), a[3]);
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+    *reinterpret_cast<uint2*>(dst + p * D) = make_uint2(a[0][p] | (a[1][p] << 16), a[2][p] | (a[3][p] << 16));
+}
+
+template <int D>
+struct SplitTile {  // an LDS stage of kScoreTile such rows
+  static constexpr int ROW = 3 * D;                  // bf16 elements per row
+  static constexpr int ROWB = 2 * ROW;               // bytes
+  static constexpr int CPR = ROWB / 16;              // 16-byte chunks per row
+  static constexpr int XM = D / 8 - 1;               // chunk c of row r is stored at c ^ (r & XM), inside its part
+  static constexpr int ELEMS = kScoreTile * ROW;
+  static constexpr int NKS = D / 16;
+  using M = Mfma<uint16_t>;
+
+  // Copy rows src[0 .. kScoreTile) (rows at or past `valid` >= 1 repeat row
+  // valid - 1) by `waves` wavefronts; the caller waits (dma_wait, barrier).
+  template <int WAVES>
+  __device__ static inline void copy(uint16_t* lds, const uint16_t* src, int valid) {
+    static_assert(CPR % WAVES == 0, "whole copies per wavefront");
+    const int w = wave_id(), ln = threadIdx.x & 63;
+    const uint64_t b = reinterpret_cast<uint64_t>(src);
+    const void* base = reinterpret_cast<const void*>(((uint64_t)(uint32_t)uniform((int)(b >> 32)) << 32) |
+                                                     (uint32_t)uniform((int)(uint32_t)b));
+#pragma unroll
+    for (int j = 0; j < CPR / WAVES; ++j) {
+      const int J = w * (CPR / WAVES) + j, slot = J * 64 + ln;
+      const int row = slot / CPR, c = slot % CPR;
+      dma16_opaque_s(base, (uint32_t)(min(row, valid - 1) * ROWB + ((c ^ (row & XM)) << 4)), lds + J * 512);
+    }
+  }
+  // The three parts of row r's k-step ks.
+  __device__ static inline void frags(bf16x8 (&f)[3], const uint16_t* lds, int r, int ks, int half) {
+    const char* row = reinterpret_cast<const char*>(lds) + r * ROWB + (((2 * ks + half) ^ (r & XM)) << 4);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) f[p] = *reinterpret_cast<const bf16x8*>(row + p * 2 * D);
+  }
+  __device__ static inline bf16x8 frag0(const uint16_t* lds, int r, int ks, int half) {
+    return *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(lds) + r * ROWB +
+                                            (((2 * ks + half) ^ (r & XM)) << 4));
+  }
+  // Row `row`'s parts of every k-step, from memory (register operand).
+  __device__ static inline void gload_all(bf16x8 (&f)[NKS][3], const uint16_t* row, int half) {
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) f[ks][p] = M::gload(row + p * D + ks * 16 + half * 8);
+  }
+  // One 32-row block of a stage against a register block.  The products with
+  // a middle or last part of every k-step come first, while the sum is small
+  // (below 2^-7 of the whole) and so are its roundings, then the leading
+  // parts' products; the leading fragments are read from LDS again for them.
+  __device__ static inline floatx16 mma(const uint16_t* lds, int r, int half, const bf16x8 (&b)[NKS][3]) {
+    floatx16 acc = floatx16{};
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      bf16x8 a[3];
+      frags(a, lds, r, ks, half);
+      acc = M::mma(a[2], b[ks][0], acc);
+      acc = M::mma(a[0], b[ks][2], acc);
+      acc = M::mma(a[1], b[ks][1], acc);
+      acc = M::mma(a[1], b[ks][0], acc);
+      acc = M::mma(a[0], b[ks][1], acc);
+    }
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) acc = M::mma(frag0(lds, r, ks, half), b[ks][0], acc);
+    return acc;
+  }
+};
 
 }  // namespace omnimem

@@ -39,16 +39,6 @@ __device__ inline float max16(const floatx16& v) {
 }
 
 
-// Interleave `nm` MFMAs with the VALU work of the same basic block:
-// groups of one MFMA followed by `nv` VALU instructions.
-#define OMNIMEM_INTERLEAVE(nm, nv)                          \
-  do {                                                      \
-    _Pragma("unroll") for (int _i = 0; _i < (nm); ++_i) {   \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    \
-      __builtin_amdgcn_sched_group_barrier(0x002, (nv), 0); \
-    }                                                       \
-  } while (0)
-
 __device__ inline float max3f(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
 // Request the LDS fragments of one 32-row block for all k-steps.
@@ -92,6 +82,25 @@ __device__ inline void online_update(const floatx16& acc, float sl2, float& m, f
   m = mnew;
 }
 
+
+// fp32 rows as three-part bf16 rows (SplitTile), written by split_rows.
+struct SplitRows {
+  const uint16_t* q;  // [L][Hq][max_chunk][3 D]
+  const uint16_t* k;  // [L][Hkv][max_tokens][3 D]
+};
+constexpr int kSplitWaves = 8;
+constexpr int kSplitRows = 64;  // rows per workgroup of split_rows
+static_assert(kBlockRows == 32 * kSplitWaves, "32 rows per wavefront");
+
+// Stage elements and workgroup of a pass.
+template <typename T, int D> struct PassShape {
+  static constexpr bool BF16 = sizeof(T) == 2;
+  static constexpr int ELEMS = BF16 ? SwzTile<uint16_t, D>::ELEMS : SplitTile<D>::ELEMS;
+  static constexpr int THREADS = BF16 ? kThreads : 64 * kSplitWaves;
+  // wavefronts per SIMD that the registers are sized for (fp32 at head_dim
+  // 64: the parts of 32 rows leave room for two workgroups)
+  static constexpr int PER_SIMD = !BF16 && D == 64 ? 4 : 2;
+};
 
 // One pipeline phase of the LSE pass, scheduled by hand: the MFMAs of the
 // 32-key row block `row` of an LDS stage (into `out`) alternate with the
@@ -171,14 +180,14 @@ __device__ inline void lse_phase(floatx16 (&out)[2], typename M::frag (&f)[NKS],
 // Software pipeline inside each wave: the MFMAs of one 32-key row block
 // run while the exp/sum work of the previous row block executes; key tiles
 // arrive by DMA one tile ahead into the LDS stage just consumed.
-template <typename T, int D>
-__device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int h, int q0, int kr0, int kr1,
-                                   int64_t row, int seg, T* kt0, T* kt1, float2* __restrict__ part) {
+template <int D>
+__device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int, int h, int q0, int kr0, int kr1,
+                                   int64_t row, int seg, uint16_t* kt0, uint16_t* kt1, const SplitRows&,
+                                   float2* __restrict__ part) {
+  using T = uint16_t;
   using M = Mfma<T>;
   using Tl = SwzTile<T, D>;
   constexpr int NKS = D / M::KSTEP;
-  constexpr int NV = 2;                   // VALU per MFMA in the compiler-scheduled (fp32) path
-  constexpr bool kHandSched = NKS <= 16;  // bf16: hand-interleaved phases
   const int C = Ld.n_chunk, N = Ld.n, nc = Ld.n_cache;
 
   const int wave = wave_id(), lane = threadIdx.x & 63, half = lane >> 5;
@@ -233,17 +242,15 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int h, i
   __syncthreads();            // both first tiles landed in LDS for every wave
   if (active && kr0 < kend_wave) {
     mma_rows<M, Tl>(acc0, kt0, arow, half, qf);
-    if constexpr (kHandSched) {
-      load_frags<M, Tl>(fA, kt0, 32 + arow, half);
-      // Reference of each query: the largest score among the segment's
-      // first 32 keys.  A lane's visible keys form a prefix of the
-      // segment's keys, so a lane with any visible key has one there.
-      if (need_mask(kr0)) apply_mask(acc0, kr0);
+    load_frags<M, Tl>(fA, kt0, 32 + arow, half);
+    // Reference of each query: the largest score among the segment's
+    // first 32 keys.  A lane's visible keys form a prefix of the
+    // segment's keys, so a lane with any visible key has one there.
+    if (need_mask(kr0)) apply_mask(acc0, kr0);
 #pragma unroll
-      for (int cb = 0; cb < 2; ++cb) {
-        const float mx = fmaxf(max16(acc0[cb]), wave_xor32(max16(acc0[cb])));
-        m[cb] = fmaxf(-1e30f, mx * sl2);
-      }
+    for (int cb = 0; cb < 2; ++cb) {
+      const float mx = fmaxf(max16(acc0[cb]), wave_xor32(max16(acc0[cb])));
+      m[cb] = fmaxf(-1e30f, mx * sl2);
     }
   }
   // One tile t in `cur`; tile t+1 is in (or on its way to) `nxt`.
@@ -253,14 +260,7 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int h, i
     // phase A: MFMAs of key rows 32..63 of tile t || exp/sum of rows 0..31
     if (busy) {
       if (need_mask(t)) apply_mask(acc0, t);
-      if constexpr (kHandSched) {
-        lse_phase<M, Tl, false>(acc1, fA, half, qf, acc0, sl2, m, lsum, cur, 0, fB);
-      } else {
-        mma_rows<M, Tl>(acc1, cur, 32 + arow, half, qf);
-        online_update(acc0[0], sl2, m[0], lsum[0]);
-        online_update(acc0[1], sl2, m[1], lsum[1]);
-        OMNIMEM_INTERLEAVE(16, NV);
-      }
+      lse_phase<M, Tl, false>(acc1, fA, half, qf, acc0, sl2, m, lsum, cur, 0, fB);
     }
     dma_wait();
     __syncthreads();  // tile t+1 landed; every wave is done with `cur`
@@ -270,15 +270,8 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int h, i
     if (busy) {
       if (need_mask(t + 32)) apply_mask(acc1, t + 32);
       if (has_next && t + kTile < kend_wave) {
-        if constexpr (kHandSched) {
-          load_frags<M, Tl>(fB, nxt, arow, half);
-          lse_phase<M, Tl, true>(acc0, fB, half, qf, acc1, sl2, m, lsum, nxt, 32 + arow, fA);
-        } else {
-          mma_rows<M, Tl>(acc0, nxt, arow, half, qf);
-          online_update(acc1[0], sl2, m[0], lsum[0]);
-          online_update(acc1[1], sl2, m[1], lsum[1]);
-          OMNIMEM_INTERLEAVE(16, NV);
-        }
+        load_frags<M, Tl>(fB, nxt, arow, half);
+        lse_phase<M, Tl, true>(acc0, fB, half, qf, acc1, sl2, m, lsum, nxt, 32 + arow, fA);
       } else {
         online_update(acc1[0], sl2, m[0], lsum[0]);
         online_update(acc1[1], sl2, m[1], lsum[1]);
@@ -289,29 +282,27 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int h, i
     step(t, kt0, kt1);
     if (t + kTile < kr1) step(t + kTile, kt1, kt0);
   }
-  if constexpr (kHandSched) {
-    // Later scores exceed the reference by far less than the sums' headroom
-    // for any realistic input; a segment whose sums still leave it is redone
-    // tile by tile with the reference moved to every block's maximum.
-    const bool bad = active && !(lsum[0] < 0x1p100f && lsum[1] < 0x1p100f);
-    if (__syncthreads_or(bad)) {  // also: every wave is done with the stages
-      m[0] = m[1] = -1e30f;
-      lsum[0] = lsum[1] = 0.0f;
-      for (int t = kr0; t < kr1; t += kTile) {
-        Tl::copy(kt0, k + (int64_t)t * kv_rs, kv_rs, min(kTile, N - t), plan);
-        dma_wait();
-        __syncthreads();
-        if (active && t < kend_wave) {
+  // Later scores exceed the reference by far less than the sums' headroom
+  // for any realistic input; a segment whose sums still leave it is redone
+  // tile by tile with the reference moved to every block's maximum.
+  const bool bad = active && !(lsum[0] < 0x1p100f && lsum[1] < 0x1p100f);
+  if (__syncthreads_or(bad)) {  // also: every wave is done with the stages
+    m[0] = m[1] = -1e30f;
+    lsum[0] = lsum[1] = 0.0f;
+    for (int t = kr0; t < kr1; t += kTile) {
+      Tl::copy(kt0, k + (int64_t)t * kv_rs, kv_rs, min(kTile, N - t), plan);
+      dma_wait();
+      __syncthreads();
+      if (active && t < kend_wave) {
 #pragma unroll
-          for (int rb = 0; rb < 2; ++rb) {
-            mma_rows<M, Tl>(acc0, kt0, rb * 32 + arow, half, qf);
-            if (need_mask(t + rb * 32)) apply_mask(acc0, t + rb * 32);
-            online_update(acc0[0], sl2, m[0], lsum[0]);
-            online_update(acc0[1], sl2, m[1], lsum[1]);
-          }
+        for (int rb = 0; rb < 2; ++rb) {
+          mma_rows<M, Tl>(acc0, kt0, rb * 32 + arow, half, qf);
+          if (need_mask(t + rb * 32)) apply_mask(acc0, t + rb * 32);
+          online_update(acc0[0], sl2, m[0], lsum[0]);
+          online_update(acc0[1], sl2, m[1], lsum[1]);
         }
-        __syncthreads();
       }
+      __syncthreads();
     }
   }
   if (!active) return;
@@ -326,16 +317,80 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int h, i
   }
 }
 
+// The same for fp32 rows, as three-part products (SplitTile): eight
+// wavefronts keep 32 queries each; per tile, the MFMAs of both 32-key blocks,
+// then their exponentials under a running maximum (the largest terms' exponents
+// near 0, where they round least).  Bound by the MFMAs, six per k-step of
+// 16.  2 layers x 16 heads, 1024 queries, 3072 + 1024 keys of width 64: 104 us
+// (234 us with the 32x32x2 fp32 MFMA), the column sums 86 us (174 us); one
+// layer x 28 heads, 1500 queries, 4500 keys of width 128: 243 us (516 us, with
+// 123 registers spilled) and 242 us (504 us).
+template <int D>
+__device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int l, int h, int q0, int kr0, int kr1,
+                                       int64_t row, int seg, uint16_t* kt0, uint16_t* kt1, const SplitRows& sr,
+                                       float2* __restrict__ part) {
+  using Tl = SplitTile<D>;
+  constexpr int W = kSplitWaves;
+  const int C = Ld.n_chunk, N = Ld.n, nc = Ld.n_cache;
+  const int wave = wave_id(), lane = threadIdx.x & 63, half = lane >> 5;
+  const uint16_t* q = sr.q + ((int64_t)l * dm.Hq + h) * dm.max_chunk * Tl::ROW;
+  const uint16_t* k = sr.k + ((int64_t)l * dm.Hkv + h / dm.G) * dm.max_tokens * Tl::ROW;
+  const int qw = q0 + wave * 32;
+  const bool active = qw < C;
+  const int kend_wave = min(kr1, dm.causal ? min(N, nc + min(qw + 32, C)) : N);
+  auto copy = [&](uint16_t* lds, int t) { Tl::template copy<W>(lds, k + (int64_t)t * Tl::ROW, min(kTile, N - t)); };
+  copy(kt0, kr0);
+  bf16x8 qf[Tl::NKS][3];
+  Tl::gload_all(qf, q + (int64_t)min(qw + (lane & 31), C - 1) * Tl::ROW, half);
+  const float sl2 = Ld.scale_log2;
+  float m = -1e30f, lsum = 0.0f;
+  auto scores = [&](const uint16_t* lds, int kb, int rb) {
+    floatx16 acc = Tl::mma(lds, rb * 32 + (lane & 31), half, qf);
+    if (kb + 32 > kend_wave || (dm.causal && kb + 31 - nc > qw)) {
+      const int base = kb + half * 4;
+      int lim = kend_wave - 1 - base;
+      if (dm.causal) lim = min(lim, qw + (lane & 31) + nc - base);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = (r >> 2) * 8 + (r & 3) <= lim ? acc[r] : -INFINITY;
+    }
+    return acc;
+  };
+  auto step = [&](int t, uint16_t* cur, uint16_t* nxt) {
+    dma_wait();
+    __syncthreads();  // tile t landed; every wave is done with the other stage
+    if (t + kTile < kr1) copy(nxt, t + kTile);
+    if (!active || t >= kend_wave) return;
+    const floatx16 a0 = scores(cur, t, 0), a1 = scores(cur, t + 32, 1);
+    online_update(a0, sl2, m, lsum);
+    online_update(a1, sl2, m, lsum);
+  };
+  for (int t = kr0; t < kr1; t += 2 * kTile) {
+    step(t, kt0, kt1);
+    if (t + kTile < kr1) step(t + kTile, kt1, kt0);
+  }
+  if (!active) return;
+  const float m2 = wave_xor32(m), l2 = wave_xor32(lsum);
+  const float mt = fmaxf(m, m2);
+  const float lt = lsum * __builtin_amdgcn_exp2f(m - mt) + l2 * __builtin_amdgcn_exp2f(m2 - mt);
+  const int my_q = qw + (lane & 31);
+  if (half == 0 && my_q < C) part[(row * kMaxSeg + seg) * kBlockRows + (my_q - q0)] = make_float2(mt, lt);
+}
+
 // Pass 1 over the plan's tiles (rows = (layer, head, 256-query block),
 // tiles = the block's visible 64-key tiles): each workgroup walks its tile
 // interval row by row.  Consecutive workgroups share rows and heads, so
 // their logical ids go to one XCD's L2.
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads, 2) void lse_pass(const LayerDesc* __restrict__ layers, Dims dm, PassPlan pl,
-                                                        float2* __restrict__ part) {
-  using Tl = SwzTile<T, D>;
-  __shared__ __attribute__((aligned(16))) T kt0[Tl::ELEMS];
-  __shared__ __attribute__((aligned(16))) T kt1[Tl::ELEMS];
+__global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_SIMD)) void lse_pass(const LayerDesc* __restrict__ layers, Dims dm,
+                                                                          PassPlan pl, SplitRows sr,
+                                                                          float2* __restrict__ part) {
+  using Sh = PassShape<T, D>;
+  __shared__ __attribute__((aligned(256))) uint16_t kt0[Sh::ELEMS];
+  __shared__ __attribute__((aligned(256))) uint16_t kt1[Sh::ELEMS];
+  auto segment = [&](auto&&... args) {
+    if constexpr (Sh::BF16) lse_segment<D>(args...);
+    else lse_segment_f32<D>(args...);
+  };
   const int i = gridDim.x % kXcds == 0 ? xcd_swizzle(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   if (pl.c == 0) {  // row mode: row i, whole
     if (i >= pl.W) return;
@@ -350,7 +405,7 @@ __global__ __launch_bounds__(kThreads, 2) void lse_pass(const LayerDesc* __restr
     const int h = (int)((i - Ld.lse_rbase) / nb), b = (int)((i - Ld.lse_rbase) % nb);
     const int q0 = b * kBlockRows;
     const int kend_blk = dm.causal ? min(Ld.n, Ld.n_cache + min(q0 + kBlockRows, Ld.n_chunk)) : Ld.n;
-    lse_segment<T, D>(Ld, dm, h, q0, 0, kend_blk, ((int64_t)l * dm.Hq + h) * dm.qb + b, 0, kt0, kt1, part);
+    segment(Ld, dm, l, h, q0, 0, kend_blk, ((int64_t)l * dm.Hq + h) * dm.qb + b, 0, kt0, kt1, sr, part);
     return;
   }
   bool first = true;
@@ -374,8 +429,8 @@ __global__ __launch_bounds__(kThreads, 2) void lse_pass(const LayerDesc* __restr
       const int q0 = b * kBlockRows;
       const int kend_blk = dm.causal ? min(Ld.n, Ld.n_cache + min(q0 + kBlockRows, Ld.n_chunk)) : Ld.n;
       if (!first) __syncthreads();  // every wave is done with the stages of the previous segment
-      lse_segment<T, D>(Ld, dm, h, q0, ta * kTile, min(tb * kTile, kend_blk),
-                        ((int64_t)l * dm.Hq + h) * dm.qb + b, plan_seg(pl, g - ta, g), kt0, kt1, part);
+      segment(Ld, dm, l, h, q0, ta * kTile, min(tb * kTile, kend_blk), ((int64_t)l * dm.Hq + h) * dm.qb + b,
+              plan_seg(pl, g - ta, g), kt0, kt1, sr, part);
       g += tb - ta;
       ta = 0;
       if (++b * kBlockRows >= Ld.n_chunk) {
@@ -430,8 +485,9 @@ __global__ __launch_bounds__(256) void lse_merge(const LayerDesc* __restrict__ l
 }
 
 // cs[cb] += sum over the lane's 16 query rows of exp2(sl2 * score - lse2).
-__device__ inline void colsum_update(const floatx16 (&acc)[2], const float* lse2_rows, int half, float sl2,
-                                     float (&cs)[2]) {
+template <int CB>
+__device__ inline void colsum_update(const floatx16 (&acc)[CB], const float* lse2_rows, int half, float sl2,
+                                     float (&cs)[CB]) {
   float nl[16];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -439,7 +495,7 @@ __device__ inline void colsum_update(const floatx16 (&acc)[2], const float* lse2
     nl[j * 4 + 0] = -v[0]; nl[j * 4 + 1] = -v[1]; nl[j * 4 + 2] = -v[2]; nl[j * 4 + 3] = -v[3];
   }
 #pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
+  for (int cb = 0; cb < CB; ++cb) {
     float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; r += 2) {
@@ -520,15 +576,15 @@ __device__ inline void colsum_phase(floatx16 (&out)[2], const T* lds, int row, i
 // over 16 query rows per tile.  Software pipeline inside each wave: the
 // MFMAs of one 32-query half run while the exp/sum work of the previous
 // half executes; query tiles arrive by DMA one tile ahead.
-template <typename T, int D>
+template <int D>
 __device__ inline void colsum_segment(const LayerDesc& Ld, const Dims& dm, int l, int h, int k0, int qstart,
-                                      int C, int64_t row, int seg, T* qt0, T* qt1, float (&lse2)[3][kTile],
-                                      const float* __restrict__ lse2_all, float* __restrict__ part) {
+                                      int C, int64_t row, int seg, uint16_t* qt0, uint16_t* qt1,
+                                      float (&lse2)[3][kTile], const SplitRows&, const float* __restrict__ lse2_all,
+                                      float* __restrict__ part) {
+  using T = uint16_t;
   using M = Mfma<T>;
   using Tl = SwzTile<T, D>;
   constexpr int NKS = D / M::KSTEP;
-  constexpr int NV = 2;                   // VALU per MFMA in the compiler-scheduled (fp32) path
-  constexpr bool kHandSched = NKS <= 16;  // bf16: hand-interleaved phases
   const int N = Ld.n, nc = Ld.n_cache;
   const int wave = wave_id(), lane = threadIdx.x & 63, half = lane >> 5;
   const int g = h / dm.G;
@@ -602,13 +658,7 @@ __device__ inline void colsum_segment(const LayerDesc& Ld, const Dims& dm, int l
       // phase A: MFMAs of row block 1 of tile qt || exp/sum of row block 0
       if (busy) {
         if (need_mask(qt)) apply_mask(acc0, qt);
-        if constexpr (kHandSched) {
-          colsum_phase<M, Tl>(acc1, cur, 32 + arow, half, kf, acc0, &lse2[slot][0], sl2, cs);
-        } else {
-          mma_rows<M, Tl>(acc1, cur, 32 + arow, half, kf);
-          colsum_update(acc0, &lse2[slot][0], half, sl2, cs);
-          OMNIMEM_INTERLEAVE(16, NV);
-        }
+        colsum_phase<M, Tl>(acc1, cur, 32 + arow, half, kf, acc0, &lse2[slot][0], sl2, cs);
       }
       if (has_next && threadIdx.x < kTile) lse2[next_slot][threadIdx.x] = lse_or_inf(qt + kTile, lse_next);
     };
@@ -628,13 +678,7 @@ __device__ inline void colsum_segment(const LayerDesc& Ld, const Dims& dm, int l
       const bool busy_next = has_next && busy_at(qt + kTile);
       if (busy && need_mask(qt + 32)) apply_mask(acc1, qt + 32);
       if (busy && busy_next) {
-        if constexpr (kHandSched) {
-          colsum_phase<M, Tl>(acc0, nxt, arow, half, kf, acc1, &lse2[slot][32], sl2, cs);
-        } else {
-          mma_rows<M, Tl>(acc0, nxt, arow, half, kf);
-          colsum_update(acc1, &lse2[slot][32], half, sl2, cs);
-          OMNIMEM_INTERLEAVE(16, NV);
-        }
+        colsum_phase<M, Tl>(acc0, nxt, arow, half, kf, acc1, &lse2[slot][32], sl2, cs);
       } else if (busy) {
         colsum_update(acc1, &lse2[slot][32], half, sl2, cs);
       } else if (busy_next) {
@@ -659,15 +703,85 @@ __device__ inline void colsum_segment(const LayerDesc& Ld, const Dims& dm, int l
   if (key < N) part[(row * kMaxSeg + seg) * kBlockRows + (key - k0)] = half ? cs[1] : cs[0];
 }
 
+// The same for fp32 rows, as three-part products: eight wavefronts keep 32
+// keys each.
+template <int D>
+__device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, int l, int h, int k0, int qstart,
+                                          int C, int64_t row, int seg, uint16_t* qt0, uint16_t* qt1,
+                                          float (&lse2)[3][kTile], const SplitRows& sr,
+                                          const float* __restrict__ lse2_all, float* __restrict__ part) {
+  using Tl = SplitTile<D>;
+  constexpr int W = kSplitWaves;
+  const int N = Ld.n, nc = Ld.n_cache;
+  const int wave = wave_id(), lane = threadIdx.x & 63, half = lane >> 5;
+  const uint16_t* q = sr.q + ((int64_t)l * dm.Hq + h) * dm.max_chunk * Tl::ROW;
+  const uint16_t* k = sr.k + ((int64_t)l * dm.Hkv + h / dm.G) * dm.max_tokens * Tl::ROW;
+  const float* lse2_lh = lse2_all + ((int64_t)l * dm.Hq + h) * dm.max_chunk;
+  const int kw = k0 + wave * 32;
+  const bool active = kw < N;
+  const int qfirst_wave = dm.causal ? max(0, kw - nc) : 0;
+  // normaliser of tile row threadIdx.x (rows past the slice: probability 0)
+  auto load_lse = [&](int qt) {
+    const float v = gload<float>(lse2_lh + min(qt + (int)(threadIdx.x & 63), C - 1));
+    return qt + (int)(threadIdx.x & 63) < C ? v : INFINITY;
+  };
+  auto copy = [&](uint16_t* lds, int t) { Tl::template copy<W>(lds, q + (int64_t)t * Tl::ROW, min(kTile, C - t)); };
+  float lse_next = 0.0f;
+  if (qstart < C) {
+    copy(qt0, qstart);
+    lse_next = load_lse(qstart);
+  }
+  bf16x8 kf[Tl::NKS][3];
+  Tl::gload_all(kf, k + (int64_t)min(kw + (lane & 31), N - 1) * Tl::ROW, half);
+  const float sl2 = Ld.scale_log2;
+  float cs[1] = {0.0f};
+  auto step = [&](int qt, int i, uint16_t* cur, uint16_t* nxt) {
+    if (threadIdx.x < kTile) lse2[i][threadIdx.x] = lse_next;
+    dma_wait();
+    __syncthreads();  // tile qt and its normalisers landed; every wave is done with the other stage
+    if (qt + kTile < C) {
+      copy(nxt, qt + kTile);
+      lse_next = load_lse(qt + kTile);
+    }
+    if (!active || qt + kTile <= qfirst_wave) return;
+    floatx16 acc[2][1];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      acc[rb][0] = Tl::mma(cur, rb * 32 + (lane & 31), half, kf);
+      const int qb = qt + rb * 32;
+      if (dm.causal && kw + 31 - nc > qb) {
+        const int dlim = kw + (lane & 31) - nc - qb - half * 4;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[rb][0][r] = ((r >> 2) * 8 + (r & 3)) >= dlim ? acc[rb][0][r] : -INFINITY;
+      }
+    }
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) colsum_update(acc[rb], &lse2[i][rb * 32], half, sl2, cs);
+  };
+  for (int qt = qstart; qt < C; qt += 2 * kTile) {
+    step(qt, 0, qt0, qt1);
+    if (qt + kTile < C) step(qt + kTile, 1, qt1, qt0);
+  }
+  if (!active) return;
+  const float t = cs[0] + wave_xor32(cs[0]);
+  const int key = kw + (lane & 31);
+  if (half == 0 && key < N) part[(row * kMaxSeg + seg) * kBlockRows + (key - k0)] = t;
+}
+
 // Pass 2 over the plan's tiles (rows = (layer, head, 256-key block), tiles
 // = the 64-query tiles that see a key of the block), walked like lse_pass.
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads, 2) void colsum_pass(const LayerDesc* __restrict__ layers, Dims dm,
-                                                           PassPlan pl, const float* __restrict__ lse2_all,
-                                                           float* __restrict__ part) {
-  using Tl = SwzTile<T, D>;
-  __shared__ __attribute__((aligned(16))) T qt0[Tl::ELEMS];
-  __shared__ __attribute__((aligned(16))) T qt1[Tl::ELEMS];
+__global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_SIMD)) void colsum_pass(const LayerDesc* __restrict__ layers, Dims dm,
+                                                                             PassPlan pl, SplitRows sr,
+                                                                             const float* __restrict__ lse2_all,
+                                                                             float* __restrict__ part) {
+  using Sh = PassShape<T, D>;
+  __shared__ __attribute__((aligned(256))) uint16_t qt0[Sh::ELEMS];
+  __shared__ __attribute__((aligned(256))) uint16_t qt1[Sh::ELEMS];
+  auto segment = [&](auto&&... args) {
+    if constexpr (Sh::BF16) colsum_segment<D>(args...);
+    else colsum_segment_f32<D>(args...);
+  };
   // normalisers: three slots, because phase B of tile i still reads slot i
   // while a faster wave already stores tile i + 2's values
   __shared__ __attribute__((aligned(16))) float lse2[3][kTile];
@@ -684,8 +798,8 @@ __global__ __launch_bounds__(kThreads, 2) void colsum_pass(const LayerDesc* __re
     const int nb = (Ld.n + kBlockRows - 1) / kBlockRows;
     const int h = (int)((i - Ld.cs_rbase) / nb), b = (int)((i - Ld.cs_rbase) % nb);
     const int t0 = cs_first_tile(Ld.n_cache, b, dm.causal);
-    colsum_segment<T, D>(Ld, dm, l, h, b * kBlockRows, t0 * kTile, Ld.n_chunk, ((int64_t)l * dm.Hq + h) * dm.kb + b, 0,
-                         qt0, qt1, lse2, lse2_all, part);
+    segment(Ld, dm, l, h, b * kBlockRows, t0 * kTile, Ld.n_chunk, ((int64_t)l * dm.Hq + h) * dm.kb + b, 0, qt0, qt1,
+            lse2, sr, lse2_all, part);
     return;
   }
   bool first = true;
@@ -707,9 +821,8 @@ __global__ __launch_bounds__(kThreads, 2) void colsum_pass(const LayerDesc* __re
       const int tb = (int)min((int64_t)tiles, ta + (gend - g));
       const int t0 = cs_first_tile(Ld.n_cache, b, dm.causal);
       if (!first) __syncthreads();  // every wave is done with the stages of the previous segment
-      colsum_segment<T, D>(Ld, dm, l, h, b * kBlockRows, (t0 + ta) * kTile, min(Ld.n_chunk, (t0 + tb) * kTile),
-                           ((int64_t)l * dm.Hq + h) * dm.kb + b, plan_seg(pl, g - ta, g), qt0, qt1, lse2,
-                           lse2_all, part);
+      segment(Ld, dm, l, h, b * kBlockRows, (t0 + ta) * kTile, min(Ld.n_chunk, (t0 + tb) * kTile),
+              ((int64_t)l * dm.Hq + h) * dm.kb + b, plan_seg(pl, g - ta, g), qt0, qt1, lse2, sr, lse2_all, part);
       g += tb - ta;
       ta = 0;
       if (++b * kBlockRows >= Ld.n) {
@@ -763,15 +876,51 @@ __global__ void head_sum(const LayerDesc* __restrict__ layers, Dims dm, PassPlan
   a[((int64_t)l * dm.Hkv + g) * dm.max_tokens + j] = sum;
 }
 
+// fp32 queries and keys of every layer as three-part rows: four elements per
+// thread, the query heads' rows, then the KV heads'.
+template <int D>
+__global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ layers, Dims dm, uint16_t* __restrict__ sq,
+                                                  uint16_t* __restrict__ sk) {
+  constexpr int TPR = D / 4, RPB = 256 / TPR;  // threads per row, rows per workgroup and step
+  const int l = blockIdx.z, head = blockIdx.y;
+  const LayerDesc& Ld = layers[l];
+  const bool is_q = head < dm.Hq;
+  const int h = is_q ? head : head - dm.Hq;
+  const int rows = is_q ? Ld.n_chunk : Ld.n;
+  const float* src = reinterpret_cast<const float*>(is_q ? Ld.q : Ld.k) + (int64_t)h * (is_q ? Ld.q_hs : Ld.kv_hs);
+  const int64_t rs = is_q ? Ld.q_rs : Ld.kv_rs;
+  uint16_t* dst = is_q ? sq + ((int64_t)l * dm.Hq + h) * dm.max_chunk * 3 * D
+                       : sk + ((int64_t)l * dm.Hkv + h) * dm.max_tokens * 3 * D;
+  const int e = (int)threadIdx.x % TPR * 4;
+  constexpr int NP = kSplitRows / RPB;
+  uint4 v[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int r = (int)blockIdx.x * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
+    if (r < rows) v[p] = gload16(src + (int64_t)r * rs + e);
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int r = (int)blockIdx.x * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
+    if (r < rows) store_split(dst + (int64_t)r * 3 * D + e, D, v[p]);
+  }
+}
+
 template <typename T, int D>
 void launch_typed(const Dims& dm, const LayerDesc* desc, const Workspace& ws, const PassPlan& lp,
                   const PassPlan& cp, float* lse_out, float* a, hipStream_t st) {
+  constexpr int kTh = PassShape<T, D>::THREADS;
+  const SplitRows sr{ws.split_q, ws.split_k};
+  if constexpr (sizeof(T) == 4) {
+    const dim3 gs((unsigned)((std::max(dm.max_tokens, dm.max_chunk) + kSplitRows - 1) / kSplitRows), dm.Hq + dm.Hkv, dm.L);
+    OMNIMEM_LAUNCH(ws, K_SPLIT, st, split_rows<D><<<gs, 256, 0, st>>>(desc, dm, ws.split_q, ws.split_k));
+  }
   if (lp.W > 0)
-    OMNIMEM_LAUNCH(ws, K_LSE, st, lse_pass<T, D><<<lp.P, kThreads, 0, st>>>(desc, dm, lp, ws.lse_part));
+    OMNIMEM_LAUNCH(ws, K_LSE, st, lse_pass<T, D><<<lp.P, kTh, 0, st>>>(desc, dm, lp, sr, ws.lse_part));
   dim3 gm((unsigned)((dm.max_chunk + 255) / 256), dm.Hq, dm.L);
   OMNIMEM_LAUNCH(ws, K_LSE_MERGE, st, lse_merge<<<gm, 256, 0, st>>>(desc, dm, lp, ws.lse_part, ws.lse2, lse_out));
   if (cp.W > 0)
-    OMNIMEM_LAUNCH(ws, K_COLSUM, st, colsum_pass<T, D><<<cp.P, kThreads, 0, st>>>(desc, dm, cp, ws.lse2, ws.part));
+    OMNIMEM_LAUNCH(ws, K_COLSUM, st, colsum_pass<T, D><<<cp.P, kTh, 0, st>>>(desc, dm, cp, sr, ws.lse2, ws.part));
   dim3 g3((unsigned)((dm.max_tokens + 255) / 256), dm.Hkv, dm.L);
   OMNIMEM_LAUNCH(ws, K_HEADSUM, st, head_sum<<<g3, 256, 0, st>>>(desc, dm, cp, ws.part, a));
 }
