@@ -863,15 +863,30 @@ __global__ void hidden_finish(const LayerDesc* __restrict__ layers, Dims dm, con
 // over lane halves and waves through LDS, merged into best once per tile).
 // Inside a wave, the MFMAs of one 32-row column block of a tile run while
 // the previous column block's products become cosines, across the per-tile
-// barrier (the score passes' software pipeline).  Register rows and tile
+// barrier (the score passes' software pipeline).  Three stages: two tiles
+// have landed while the third is copied, so a phase can request its
+// successor's first fragments across the barrier and no phase starts with an
+// exposed LDS read.  Register rows and tile
 // rows past the segment carry NaN inverse norms, and a row's pair with itself
 // is set to NaN; fmaxf ignores both.
+// Bounds: 32 cycles of matrix core per MFMA against 8 vector instructions
+// (28 cycles and their issue), two waves per SIMD.  28 layers x 4 heads x
+// 6144 rows of width 128 (0.36 TFLOP): 484-513 us with two stages and tiles
+// alone shared out, 442 us so (366 us on all-equal rows, whose lower power
+// keeps the clock up; 265 us with the cosines left out); one layer 35 -> 28
+// us, 3 layers x 2 heads x 512 rows 18 -> 13 us.
 constexpr int kSymBlock = 256;
 
-// Tiles of a segment of K rows: register block I sees tiles 4I .. kt-1.
-__device__ inline int64_t sym_seg_tiles(int K) {
+// Cost of register block I of a segment of kt tiles: its tiles 4I .. kt-1 and
+// its start-up (row list, rows, inverse norms, one after the other), counted
+// as 5 tiles; and of a whole segment of K rows.  Shares of equal tiles left
+// workgroups with many short rows last: 28 layers of 6144 rows 446 us at 2,
+// 442 at 4, 444 at 6, 451 at 13; one layer 31, 28, 27.5, 29 us.
+constexpr int kSymRowCost = 5;
+__device__ inline int sym_row_cost(int kt, int I) { return kt - 4 * I + kSymRowCost; }
+__device__ inline int64_t sym_seg_cost(int K) {
   const int64_t kt = (K + kScoreTile - 1) / kScoreTile, nb = (K + kSymBlock - 1) / kSymBlock;
-  return nb * kt - 2 * nb * (nb - 1);
+  return nb * (kt + kSymRowCost) - 2 * nb * (nb - 1);
 }
 
 __device__ inline void gatomic_max(int* p, int v) {
@@ -895,43 +910,34 @@ __device__ inline float vmax3(float a, float b, float c) {
 }
 
 // One phase of gram_sym in a wave: with MMA, the MFMAs (k-steps x the two
-// register row blocks) of the 32 tile rows from LDS row `brow` into `out`;
-// with EPI, interleaved with them (32 / (2 NKS) per MFMA), the products of
-// the previous column block `in` become cosines and enter the row maxima
-// `rmax` and the column maximum `cm`.  LDS fragments are requested two
-// k-steps ahead of their MFMAs.
+// register row blocks) of the 32 tile rows whose LDS fragments start at
+// `cur` into `out`; with EPI, interleaved with them (32 / (2 NKS) per MFMA),
+// the products of the previous column block `in` become cosines and enter
+// the row maxima `rmax` and the column maximum `cm`.  LDS fragments are
+// requested two k-steps ahead of their MFMAs, across phases: `pre` holds the
+// phase's first two on entry and the next MMA phase's (at `nxt`) on return.
 template <int NKS, bool MMA, bool EPI>
-__device__ inline void sym_phase(floatx16 (&out)[2], bf16x8 (&a)[2][NKS], const uint16_t* lds, int brow, int half,
+__device__ inline void sym_phase(floatx16 (&out)[2], bf16x8 (&a)[2][NKS], bf16x8 (&pre)[2], uint32_t cur, uint32_t nxt,
                                  floatx16 (&in)[2], float invj, float (&iv)[2][16], float (&rmax)[2][16],
                                  float& cm) {
   using M = Mfma<uint16_t>;
-  using Tl = SwzTile<uint16_t, NKS * 16>;
   constexpr int NG = 2 * NKS;     // groups, one MFMA each
   constexpr int PER = 32 / NG;    // cosines per group
-  static_assert(PER * NG == 32 && PER >= 1, "products per lane of a column block");
-  // LDS address of row brow's k-step-ks fragment in the swizzled tile: piece
-  // (2 ks + half) ^ (brow & XM) of the row, that is base ^ (ks << 5) with
-  // base the k-step-0 address (the tile starts on a ROWB boundary and the
-  // row's own offset has no bits below ROWB).  The base is rebuilt per
-  // phase rather than held across the tile loop.
-  static_assert(Tl::ROWB >= 32 * NKS, "k-step bits stay inside a row");
+  static_assert(PER * NG == 32 && PER >= 1 && NKS >= 2, "products per lane of a column block");
   typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
-  uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds + brow * Tl::ROWB +
-                  ((half ^ (brow & Tl::XM)) << 4);
-  pin(base);
-  auto frag = [&](int ks) { return *(lds_frag*)(uintptr_t)(base ^ (uint32_t)(ks << 5)); };
-  bf16x8 f[NKS];
+  auto frag = [](uint32_t base, int ks) { return *(lds_frag*)(uintptr_t)(base ^ (uint32_t)(ks << 5)); };
+  bf16x8 f[NKS + 2];
   if (MMA) __builtin_amdgcn_s_setprio(1);  // a wave in its MFMA stream issues ahead of one in the tile bookkeeping
   if (MMA) {
-    f[0] = frag(0);
-    if (NKS > 1) f[1] = frag(1);
+    f[0] = pre[0];
+    f[1] = pre[1];
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     const int ks = g >> 1, rb = g & 1;
     if (MMA) {
-      if (rb == 0 && ks + 2 < NKS) f[ks + 2] = frag(ks + 2);
+      if (rb == 0) f[ks + 2] = ks + 2 < NKS ? frag(cur, ks + 2) : frag(nxt, ks + 2 - NKS);
       pin(a[rb][ks]);
       out[rb] = M::mma(a[rb][ks], f[ks], ks ? out[rb] : floatx16{});
     }
@@ -942,18 +948,20 @@ __device__ inline void sym_phase(floatx16 (&out)[2], bf16x8 (&a)[2][NKS], const 
         const int e = g * PER + i, erb = e >> 4, r = e & 15;
         c[i] = in[erb][r] * invj * iv[erb][r];
         rmax[erb][r] = vmax(rmax[erb][r], c[i]);
-        pin(rmax[erb][r]);
       }
 #pragma unroll
       for (int i = 0; i < PER; i += 2) cm = vmax3(cm, c[i], c[i + 1]);
-      pin(cm);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (MMA) __builtin_amdgcn_s_setprio(0);
+  if (MMA) {
+    pre[0] = f[NKS];
+    pre[1] = f[NKS + 1];
+    __builtin_amdgcn_s_setprio(0);
+  }
 }
 
-template <int D, bool BY_XCD>
+template <int D>
 __global__ __launch_bounds__(256, 2) void gram_sym(const LayerDesc* __restrict__ layers, Dims dm, int on_keys,
                                                    const int* __restrict__ counts, const int* __restrict__ pos,
                                                    const float* __restrict__ inv, int* __restrict__ best) {
@@ -963,29 +971,36 @@ __global__ __launch_bounds__(256, 2) void gram_sym(const LayerDesc* __restrict__
   constexpr int NKS = D / M::KSTEP;
   constexpr int IPW = Tl::INSTR_PER_WAVE;  // DMA copies per wave and tile
   constexpr int kMaxL = 1024;
+  constexpr int kStages = 3;
   constexpr int kSlots = 4;  // column maxima of tiles t - 1 (being merged) .. t + 2 (being written)
-  __shared__ __attribute__((aligned(256))) T jt[2][Tl::ELEMS];  // stages start on row boundaries
+  __shared__ __attribute__((aligned(256))) T jt[kStages][Tl::ELEMS];  // stages start on row boundaries
   __shared__ float cmx[kSlots][4][2][kScoreTile];  // [tile][wave][lane half][tile row]
-  __shared__ int64_t lbase[kMaxL + 1];  // first tile of each layer
-  __shared__ int64_t sc[2];             // total tiles, longest row
+  __shared__ int64_t lbase[kMaxL + 1];  // cost of the layers before each layer
 
-  if (threadIdx.x == 0) {
+  const int wave = wave_id(), lane = threadIdx.x & 63, half = lane >> 5;
+  if (wave == 0) {
     int64_t w = 0;
-    int tmax = 0;
-    for (int l = 0; l < dm.L; ++l) {
-      lbase[l] = w;
-      const int kv = counts[2 * l], ka = counts[2 * l + 1];
-      w += (int64_t)dm.Hkv * (sym_seg_tiles(kv) + sym_seg_tiles(ka));
-      tmax = max(tmax, (max(kv, ka) + kScoreTile - 1) / kScoreTile);
+    if (lane == 0) lbase[0] = 0;
+    for (int l0 = 0; l0 < dm.L; l0 += 64) {
+      const int l = l0 + lane;
+      int64_t c = l < dm.L ? dm.Hkv * (sym_seg_cost(counts[2 * l]) + sym_seg_cost(counts[2 * l + 1])) : 0;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int64_t before = __shfl_up(c, o, 64);
+        if (lane >= o) c += before;
+      }
+      if (l < dm.L) lbase[l + 1] = w + c;
+      w += __shfl(c, 63, 64);
     }
-    lbase[dm.L] = w;
-    sc[0] = w;
-    sc[1] = tmax;
   }
   __syncthreads();
-  const int64_t W = sc[0];
+  // Workgroup i's share of the cost, contiguous; the workgroups of an XCD
+  // (blockIdx % 8) are neighbours, so its L2 serves the same heads to them.
+  const int64_t W = lbase[dm.L];
   const int i = gridDim.x % kXcds == 0 ? xcd_swizzle(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int wave = wave_id(), lane = threadIdx.x & 63, half = lane >> 5;
+  int64_t gt = W * i / gridDim.x;
+  const int64_t gend = W * (i + 1) / gridDim.x;
+  if (gt >= gend) return;
   // This lane's DMA pieces of a tile: copy j moves piece ln % CPR of tile
   // row (wave * IPW + j) * RPI + ln / CPR (RPI rows per copy) to its
   // swizzled place, piece (ln % CPR) ^ (row & XM); the rows come through the
@@ -995,32 +1010,39 @@ __global__ __launch_bounds__(256, 2) void gram_sym(const LayerDesc* __restrict__
   // held across the tile loop.)
   constexpr int RPI = 64 / Tl::CPR;
   static_assert((IPW * RPI) % (Tl::XM + 1) == 0 && RPI <= Tl::XM + 1, "copy swizzle is per lane");
-  bool first = true;
+  // LDS address of tile row (lane % 32)'s k-step-ks fragment in the swizzled
+  // stage 0: piece (2 ks + half) ^ (row & XM) of the row, that is
+  // frag0 ^ (ks << 5), as stages start on ROWB boundaries; row 32 + lane % 32
+  // of stage s is 32 rows and s stages further (32 is a multiple of XM + 1).
+  static_assert(Tl::ROWB >= 32 * NKS && 32 % (Tl::XM + 1) == 0, "k-step bits stay inside a row");
+  const uint32_t frag0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)&jt[0][0] +
+                         (lane & 31) * Tl::ROWB + ((half ^ (lane & 31 & Tl::XM)) << 4);
+  constexpr uint32_t kStageB = Tl::ELEMS * sizeof(T), kHalfB = kStageB / 2;
 
-  auto run_range = [&](int64_t gt, const int64_t gend) {
-    while (gt < gend) {
-      // the row holding tile gt: layer, KV head, modality, register block
-      int l = 0;
-      for (int lo = 0, hi = dm.L - 1; lo < hi;) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (lbase[mid] <= gt) lo = mid; else hi = mid - 1;
-        l = lo;
-      }
-      const int kv = counts[2 * l], ka = counts[2 * l + 1];
-      const int64_t tv = sym_seg_tiles(kv), tav = sym_seg_tiles(ka);
-      int64_t rem = gt - lbase[l];
-      const int g = (int)(rem / (tv + tav));
-      rem -= g * (tv + tav);
-      const int mu = rem >= tv ? 1 : 0;
-      if (mu) rem -= tv;
-      const int K = mu ? ka : kv;
-      const int kt = (K + kScoreTile - 1) / kScoreTile;
-      int I = 0;
-      while (rem >= kt - 4 * I) { rem -= kt - 4 * I; ++I; }
-      const int t0 = 4 * I + (int)rem;
-      const int t1 = (int)min((int64_t)kt, t0 + (gend - gt));
-      gt += t1 - t0;
-
+  // the row of work holding cost gt: layer, KV head, modality, register block
+  int l = 0;
+  for (int lo = 0, hi = dm.L - 1; lo < hi;) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (lbase[mid] <= gt) lo = mid; else hi = mid - 1;
+    l = lo;
+  }
+  l = uniform(l);
+  int kv = counts[2 * l], ka = counts[2 * l + 1];
+  const int64_t cv = sym_seg_cost(kv), cva = cv + sym_seg_cost(ka);
+  int64_t rem = gt - lbase[l];
+  int g = uniform((int)(rem / cva));
+  rem -= g * cva;
+  int mu = rem >= cv ? 1 : 0;
+  if (mu) rem -= cv;
+  int K = mu ? ka : kv, kt = (K + kScoreTile - 1) / kScoreTile;
+  int I = 0;
+  while (rem >= sym_row_cost(kt, I)) { rem -= sym_row_cost(kt, I); ++I; }
+  while (true) {
+    // the row's tiles in this workgroup's share (none, if it ends in the row's start-up cost)
+    const int64_t c1 = min((int64_t)sym_row_cost(kt, I), rem + (gend - gt));
+    gt += c1 - rem;
+    const int t0 = 4 * I + max(0, (int)rem - kSymRowCost), t1 = 4 * I + (int)c1 - kSymRowCost;
+    if (t0 < t1) {
       const LayerDesc& Ld = layers[l];
       const T* U = reinterpret_cast<const T*>(on_keys ? Ld.k : Ld.v) + (int64_t)g * Ld.kv_hs;
       const int64_t rs = Ld.kv_rs;
@@ -1028,48 +1050,59 @@ __global__ __launch_bounds__(256, 2) void gram_sym(const LayerDesc* __restrict__
       const int64_t seg_off = ((int64_t)l * dm.Hkv + g) * dm.max_tokens + (mu ? kv : 0);
       const float* invs = inv + seg_off;
       int* bst = best + seg_off;
-      if (!first) __syncthreads();  // every wave is done with the previous row's stages and maxima
-      first = false;
 
-      int pr[IPW];  // source rows of this lane's pieces of the next tile to copy
       // (byte offsets of rows in one head fit 31 bits, which the entry points check)
       const uint32_t rs_b = (uint32_t)(rs * (int64_t)sizeof(T));
-      // (rows past the segment come from the list's padding, which repeats its last row)
-      auto rows_of = [&](int t) {
+      // source rows of this lane's pieces of a tile to copy (rows past the
+      // segment come from the list's padding, which repeats its last row)
+      auto rows_of = [&](int (&pr)[IPW], int t) {
         int ln = lane;
         pin(ln);
         const int* Pt = P + (t * kScoreTile + wave * IPW * RPI);
 #pragma unroll
-        for (int j = 0; j < IPW; ++j) pr[j] = gload<int>(Pt + ((uint32_t)ln / Tl::CPR + j * RPI));
+        for (int j = 0; j < IPW; ++j) pr[j] = gload<int>(Pt + j * RPI + (uint32_t)ln / Tl::CPR);
       };
-      auto copy = [&](int buf) {
+      auto copy = [&](const int (&pr)[IPW], int stage) {
         int ln = lane;
         pin(ln);
         const uint32_t colb = (((uint32_t)ln % Tl::CPR) ^ ((uint32_t)ln / Tl::CPR)) << 4;
 #pragma unroll
         for (int j = 0; j < IPW; ++j)
           dma16_opaque_s(U, __umul24((uint32_t)pr[j], rs_b) + (colb ^ (uint32_t)(((j * RPI) & Tl::XM) << 4)),
-                         &jt[buf][(wave * IPW + j) * 64 * Tl::EPC]);
+                         &jt[stage][(wave * IPW + j) * 64 * Tl::EPC]);
       };
       auto invj_of = [&](int t, int cb) {  // inverse norm of tile row t*64 + cb*32 + lane%32 (NaN past K)
         const int row = t * kScoreTile + cb * 32 + (lane & 31);
         const float v = gload<float>(invs + (uint32_t)min(row, K - 1));
         return row < K ? v : __builtin_nanf("");
       };
-      rows_of(t0);
-      copy(0);
-      if (t0 + 1 < t1) { rows_of(t0 + 1); copy(1); }
-      if (t0 + 2 < t1) rows_of(t0 + 2);
       // this wave's 64 register rows (two 32-row blocks of the output)
       const int c0 = I * kSymBlock + wave * 64;
+      // Start-up: the list entries first, then the rows they name.  (Every
+      // wave has left the stages of the previous row: it has passed the
+      // barrier before that row's last merge.)
+      int pr[IPW];
       bf16x8 a[2][NKS];
+      {
+        int p0[IPW], p1[IPW], src[2];
+        rows_of(p0, t0);
+        if (t0 + 1 < t1) rows_of(p1, t0 + 1);
+        if (t0 + 2 < t1) rows_of(pr, t0 + 2);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) src[rb] = gload<int>(P + (uint32_t)(c0 + rb * 32 + (lane & 31)));
+        copy(p0, 0);
+        if (t0 + 1 < t1) copy(p1, 1);
+        if (t0 + 2 < t1) copy(pr, 2);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int ks = 0; ks < NKS; ++ks)
+            a[rb][ks] = M::gload(U + ((uint32_t)src[rb] * (uint32_t)rs + ks * M::KSTEP + half * M::PER_LANE));
+        if (t0 + 3 < t1) rows_of(pr, t0 + 3);
+      }
       float iv[2][16], rmax[2][16];
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
-        const int src = gload<int>(P + (uint32_t)(c0 + rb * 32 + (lane & 31)));
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
-          a[rb][ks] = M::gload(U + ((uint32_t)src * (uint32_t)rs + ks * M::KSTEP + half * M::PER_LANE));
         int ln = lane;
         pin(ln);  // the rows below are recomputed per row of work, not held across the loop
 #pragma unroll
@@ -1106,47 +1139,57 @@ __global__ __launch_bounds__(256, 2) void gram_sym(const LayerDesc* __restrict__
         }
       };
       floatx16 acc0[2], acc1[2];
+      bf16x8 pre[2];
       float cm = -INFINITY;
       dma_wait();
-      __syncthreads();  // tiles t0 and t0+1 landed
-      sym_phase<NKS, true, false>(acc0, a, jt[0], lane & 31, half, acc1, 0.0f, iv, rmax, cm);
+      __syncthreads();  // tiles t0 .. t0+2 landed
+      {
+        typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
+        pre[0] = *(lds_frag*)(uintptr_t)frag0;
+        pre[1] = *(lds_frag*)(uintptr_t)(frag0 ^ 32u);
+      }
+      sym_phase<NKS, true, false>(acc0, a, pre, frag0, frag0 + kHalfB, acc1, 0.0f, iv, rmax, cm);
+      uint32_t sb = 0;  // byte offset of tile t's stage
+      int st = 0;
       // phase A of tile t: MFMAs of its tile rows 32..63 || cosines of its rows 0..31
-      auto phase_a = [&](int t) {
+      auto phase_a = [&](int t, uint32_t nb) {
         mask_diag(acc0, t, 0);
         cm = -INFINITY;
-        sym_phase<NKS, true, true>(acc1, a, jt[(t - t0) & 1], 32 + (lane & 31), half, acc0, ij[0], iv, rmax, cm);
+        sym_phase<NKS, true, true>(acc1, a, pre, frag0 + sb + kHalfB, frag0 + nb, acc0, ij[0], iv, rmax, cm);
         cmx[t & 3][wave][half][lane & 31] = cm;
       };
       for (int t = t0; t + 1 < t1; ++t) {
-        const int st = (t - t0) & 1;
+        const uint32_t nb = st == kStages - 1 ? 0 : sb + kStageB;  // tile t+1's stage
         ijn[0] = invj_of(t + 1, 0);
         ijn[1] = invj_of(t + 1, 1);
-        phase_a(t);
+        phase_a(t, nb);
         dma_wait();
-        __syncthreads();  // tile t+1 landed; every wave is done with tile t's stage
+        __syncthreads();  // tile t+2 landed; every wave is done with tile t's stage
         pin(ijn[0]);
         pin(ijn[1]);
-        if (t + 2 < t1) {
-          copy(st);
-          if (t + 3 < t1) rows_of(t + 3);
+        if (t + 3 < t1) {
+          copy(pr, st);
+          if (t + 4 < t1) rows_of(pr, t + 4);
         }
         if (t > t0) merge(t - 1);
         // phase B: MFMAs of tile rows 0..31 of tile t+1 || cosines of rows 32..63 of tile t
         mask_diag(acc1, t, 1);
         cm = -INFINITY;
-        sym_phase<NKS, true, true>(acc0, a, jt[st ^ 1], lane & 31, half, acc1, ij[1], iv, rmax, cm);
+        sym_phase<NKS, true, true>(acc0, a, pre, frag0 + nb, frag0 + nb + kHalfB, acc1, ij[1], iv, rmax, cm);
         cmx[t & 3][wave][half][32 + (lane & 31)] = cm;
         ij[0] = ijn[0];
         ij[1] = ijn[1];
+        sb = nb;
+        st = st == kStages - 1 ? 0 : st + 1;
       }
       {  // the last tile: its phase B has no MFMAs
         const int t = t1 - 1;
-        phase_a(t);
+        phase_a(t, sb);
         __syncthreads();
         if (t > t0) merge(t - 1);
         mask_diag(acc1, t, 1);
         cm = -INFINITY;
-        sym_phase<NKS, false, true>(acc0, a, jt[0], 0, half, acc1, ij[1], iv, rmax, cm);
+        sym_phase<NKS, false, true>(acc0, a, pre, 0, 0, acc1, ij[1], iv, rmax, cm);
         cmx[t & 3][wave][half][32 + (lane & 31)] = cm;
       }
       __syncthreads();  // the last tile's maxima are in LDS
@@ -1160,30 +1203,25 @@ __global__ __launch_bounds__(256, 2) void gram_sym(const LayerDesc* __restrict__
           gatomic_max(bst + row, ord_f32(fminf(1.0f, fmaxf(-1.0f, rmax[rb][0]))));
       }
     }
-  };
-  // Unit u = (layer, KV head) goes to XCD u % 8 (with BY_XCD; otherwise the
-  // whole grid is one group), whose workgroups take its units k at a time
-  // and split their tiles evenly, so that an XCD's L2 holds the rows of k
-  // units at a time.  One call site of run_range keeps one copy of its code.
-  constexpr int kX = BY_XCD ? kXcds : 1;
-  const int units = dm.L * dm.Hkv;
-  const int px = (int)gridDim.x / kX, x = i / px, ix = i % px;
-  const int64_t per0 = max((int64_t)1, W / max(units, 1));
-  const int k = (int)max((int64_t)1, min((int64_t)8, (sc[1] * px + per0 - 1) / per0));
-  for (int u0 = x; u0 < units; u0 += k * kX) {
-    int64_t tot = 0;
-    for (int jj = 0; jj < k && u0 + jj * kX < units; ++jj) {
-      const int l = (u0 + jj * kX) / dm.Hkv;
-      tot += sym_seg_tiles(counts[2 * l]) + sym_seg_tiles(counts[2 * l + 1]);
-    }
-    const int64_t cu = (tot + px - 1) / px, ga = ix * cu, gb = min(tot, ga + cu);
-    int64_t off = 0;
-    for (int jj = 0; jj < k && u0 + jj * kX < units && off < gb; ++jj) {
-      const int u = u0 + jj * kX, l = u / dm.Hkv, g = u % dm.Hkv;
-      const int64_t per = sym_seg_tiles(counts[2 * l]) + sym_seg_tiles(counts[2 * l + 1]);
-      const int64_t lo = max(ga, off), hi = min(gb, off + per);
-      if (lo < hi) run_range(lbase[l] + g * per + (lo - off), lbase[l] + g * per + (hi - off));
-      off += per;
+    if (gt >= gend) break;
+    // the next row
+    rem = 0;
+    ++I;
+    while (I * kSymBlock >= K) {
+      I = 0;
+      if (mu == 0) {
+        mu = 1;
+      } else {
+        mu = 0;
+        if (++g == dm.Hkv) {
+          g = 0;
+          ++l;
+          kv = counts[2 * l];
+          ka = counts[2 * l + 1];
+        }
+      }
+      K = mu ? ka : kv;
+      kt = (K + kScoreTile - 1) / kScoreTile;
     }
   }
 }
@@ -1200,25 +1238,19 @@ void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, c
   }
   const dim3 glist((unsigned)((dm.max_tokens + kListRows - 1) / kListRows), dm.Hkv, dm.L);
   uint16_t* perm = ws.perm;
-  const bool by_xcd = dm.L * dm.Hkv >= 2 * kXcds && ws.gram_grid % kXcds == 0;
   if constexpr (sizeof(T) == 2) {  // bf16: each pair once, rows gathered through the row lists
     OMNIMEM_LAUNCH(ws, K_NORMS, st,
                    lists_norms<T, D, false><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts,
                                                                    perm, ws.inv_norm, ws.best));
-    if (by_xcd)
-      OMNIMEM_LAUNCH(ws, K_GRAM_SYM, st,
-                     gram_sym<D, true><<<ws.gram_grid, 256, 0, st>>>(desc, dm, on_keys, ws.counts, ws.pos,
-                                                                      ws.inv_norm, ws.best));
-    else
-      OMNIMEM_LAUNCH(ws, K_GRAM_SYM, st,
-                     gram_sym<D, false><<<ws.gram_grid, 256, 0, st>>>(desc, dm, on_keys, ws.counts, ws.pos,
-                                                                       ws.inv_norm, ws.best));
+    OMNIMEM_LAUNCH(ws, K_GRAM_SYM, st,
+                   gram_sym<D><<<ws.gram_grid, 256, 0, st>>>(desc, dm, on_keys, ws.counts, ws.pos, ws.inv_norm, ws.best));
     OMNIMEM_LAUNCH(ws, K_GRAM_FINISH, st, gram_finish<<<gtok, 256, 0, st>>>(desc, dm, ws.pos, ws.counts, ws.best, s));
     return;
   }
   OMNIMEM_LAUNCH(ws, K_NORMS, st,
                  lists_norms<T, D, true><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, perm,
                                                                 ws.inv_norm, ws.best));
+  const bool by_xcd = dm.L * dm.Hkv >= 2 * kXcds && ws.gram_grid % kXcds == 0;
   if (by_xcd)
     OMNIMEM_LAUNCH(ws, K_GRAM, st,
                    gram_pass<D, true><<<ws.gram_grid, 64 * kGramWaves, 0, st>>>(desc, dm, ws.counts, perm, ws.inv_norm, ws.best));
