@@ -75,7 +75,7 @@ struct omnimem_ctx {
   bool last_has_chunks = false;         // an append's table, chunk fields filled in
   bool last_captured = false;           // its copy was recorded into a graph, not run
   hipStream_t last_stream = nullptr;    // the stream of its copy
-  PassPlan lse_plan{0, 0}, cs_plan{0, 0};  // score-pass plans of the last table
+  PassPlan lse_plan{}, cs_plan{};  // score-pass plans of the last table
   int max_workgroups = 512;               // persistent score-pass grid: 2 per compute unit
   int calib_steps = 0;                    // steps in the calibration sums since the last reset
   int topk_path = OMNIMEM_TOPK_AUTO;
@@ -536,9 +536,9 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
   ws.stage_rows = c.inplace_stage_rows;
   const size_t elt = c.dtype == OMNIMEM_BF16 ? 2 : 4;
   if ((e = dalloc(ctx, &ws.desc, (size_t)kSlots * L)) != hipSuccess ||
-      (e = dalloc(ctx, &ws.lse_part, L * Hq * (size_t)dm.qb * kMaxSeg * kScoreBlock)) != hipSuccess ||
+      (e = dalloc(ctx, &ws.lse_part, (size_t)plan_partials((int64_t)(L * Hq) * dm.qb) * kScoreBlock)) != hipSuccess ||
       (e = dalloc(ctx, &ws.lse2, L * Hq * Cm)) != hipSuccess ||
-      (e = dalloc(ctx, &ws.part, L * Hq * (size_t)dm.kb * kMaxSeg * kScoreBlock)) != hipSuccess ||
+      (e = dalloc(ctx, &ws.part, (size_t)plan_partials((int64_t)(L * Hq) * dm.kb) * kScoreBlock)) != hipSuccess ||
       (e = dalloc(ctx, &ws.pos, L * 2 * (size_t)list_stride(T))) != hipSuccess ||
       (e = dalloc(ctx, &ws.counts, L * 2)) != hipSuccess ||
       (e = dalloc(ctx, &ws.inv_norm, L * Hkv * T)) != hipSuccess ||

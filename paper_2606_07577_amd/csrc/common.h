@@ -70,18 +70,38 @@ struct Dims {
 // differs by at most one chunk.  A chunk may hold parts of several rows;
 // each part writes a partial result for (row, segment), the segment being
 // the chunk's index minus that of the row's first tile.  c is at least
-// (longest row) / (kMaxSeg - 1), so no row has more than kMaxSeg segments.
+// (longest row) / (segs - 1), so no row has more than segs segments.
 // With many more rows than workgroup slots a plan has c = 0 ("row mode"):
 // one workgroup per row, W = the number of rows, and a single segment.
 constexpr int kScoreBlock = 256;  // rows a workgroup keeps in registers
 constexpr int kScoreTile = 64;    // rows per streamed tile
-constexpr int kMaxSeg = 4;
+// Partials (of 256 rows) kept for a pass whose context has at most
+// `capacity` rows, and the segments a row may have in a call of `rows`
+// rows.  Four fill the chip from about 170 rows on; with fewer (a short chunk, few layers or heads)
+// they would leave slots without a workgroup, so a row may have as many as
+// the partials allow (at least 4096: 8 MB and 4 MB).  Four against this, the
+// score call: 28 heads of width 128, 128 queries, 4224 keys 53 -> 38 us;
+// 256 queries, 40256 keys 346 -> 197 us; 2 layers x 16 heads of fp32 width 64, 1024
+// queries, 4096 keys 206 -> 184 us; 1 layer x 28 heads, 2048 queries
+// (224 rows) as before.
+constexpr int kMinSegs = 4, kRowSegs = 64, kMinPartials = 4096;
+__host__ __device__ inline int64_t plan_partials(int64_t capacity) {
+  return capacity * kMinSegs > kMinPartials ? capacity * kMinSegs : kMinPartials;
+}
+inline int plan_segs(int64_t capacity, int64_t rows) {
+  return (int)std::min<int64_t>(kRowSegs, plan_partials(capacity) / std::max<int64_t>(rows, 1));
+}
 constexpr int kGatherRows = 64;   // slots per tile (and workgroup) of the in-place gather and its staging
 struct PassPlan {
   int64_t W;  // tiles
   int P;      // workgroups
   int c;      // tiles per chunk
+  int segs;   // partials per row
 };
+// First partial of block b of head h in a layer whose rows start at `rbase`, n rows in blocks.
+__host__ __device__ inline int64_t plan_slot(const PassPlan& p, int64_t rbase, int h, int n, int b) {
+  return (rbase + (int64_t)h * ((n + kScoreBlock - 1) / kScoreBlock) + b) * p.segs;
+}
 // Segment of the row starting at tile `start` that holds tile g.
 __host__ __device__ inline int plan_seg(const PassPlan& p, int64_t start, int64_t g) {
   return p.c == 0 ? 0 : (int)(g / p.c - start / p.c);
@@ -223,9 +243,9 @@ void prof_mark(Profiler* p, int kernel, hipStream_t st, bool begin);
 // ---------------------------------------------------------------------------
 struct Workspace {
   LayerDesc* desc;        // [slots][L]
-  float2* lse_part;       // [L][Hq][qb][kMaxSeg][256] partial (reference, sum) in log2 units
+  float2* lse_part;       // [partials][256] partial (reference, sum) in log2 units
   float* lse2;            // [L][Hq][max_chunk] merged normaliser, log2 units
-  float* part;            // [L][Hq][kb][kMaxSeg][256] partial column sums per query head
+  float* part;            // [partials][256] partial column sums per query head
   int* pos;               // [L][2][max_tokens + kListPad] visual rows, audio rows (ascending)
   int* counts;            // [L][2]           K_v, K_a
   float* inv_norm;        // [L][Hkv][max_tokens] inverse norms, segment order

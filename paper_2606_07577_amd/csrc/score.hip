@@ -25,6 +25,7 @@ constexpr int kThreads = 256;       // 4 wavefronts
 constexpr int kRowsPerWave = 64;    // register-resident rows per wave (two 32-wide MFMA blocks)
 constexpr int kBlockRows = kScoreBlock;  // = 4 * kRowsPerWave
 constexpr int kTile = kScoreTile;        // streamed rows per LDS stage
+constexpr int kSegsAtOnce = 4;           // a row's partials that a merging thread requests together
 static_assert(kBlockRows == 4 * kRowsPerWave, "four waves per block");
 
 __device__ inline float wave_xor32(float x) { return __shfl_xor(x, 32, 64); }
@@ -182,7 +183,7 @@ __device__ inline void lse_phase(floatx16 (&out)[2], typename M::frag (&f)[NKS],
 // arrive by DMA one tile ahead into the LDS stage just consumed.
 template <int D>
 __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int, int h, int q0, int kr0, int kr1,
-                                   int64_t row, int seg, uint16_t* kt0, uint16_t* kt1, const SplitRows&,
+                                   int64_t pslot, uint16_t* kt0, uint16_t* kt1, const SplitRows&,
                                    float2* __restrict__ part) {
   using T = uint16_t;
   using M = Mfma<T>;
@@ -313,7 +314,7 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int, int
     const float lt = lsum[cb] * __builtin_amdgcn_exp2f(m[cb] - mt) + l2 * __builtin_amdgcn_exp2f(m2 - mt);
     const int my_q = qw + cb * 32 + (lane & 31);
     if (half == 0 && my_q < C)
-      part[(row * kMaxSeg + seg) * kBlockRows + (my_q - q0)] = make_float2(mt, lt);
+      part[pslot * kBlockRows + (my_q - q0)] = make_float2(mt, lt);
   }
 }
 
@@ -327,7 +328,7 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int, int
 // 123 registers spilled) and 242 us (504 us).
 template <int D>
 __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int l, int h, int q0, int kr0, int kr1,
-                                       int64_t row, int seg, uint16_t* kt0, uint16_t* kt1, const SplitRows& sr,
+                                       int64_t pslot, uint16_t* kt0, uint16_t* kt1, const SplitRows& sr,
                                        float2* __restrict__ part) {
   using Tl = SplitTile<D>;
   constexpr int W = kSplitWaves;
@@ -373,7 +374,7 @@ __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int 
   const float mt = fmaxf(m, m2);
   const float lt = lsum * __builtin_amdgcn_exp2f(m - mt) + l2 * __builtin_amdgcn_exp2f(m2 - mt);
   const int my_q = qw + (lane & 31);
-  if (half == 0 && my_q < C) part[(row * kMaxSeg + seg) * kBlockRows + (my_q - q0)] = make_float2(mt, lt);
+  if (half == 0 && my_q < C) part[pslot * kBlockRows + (my_q - q0)] = make_float2(mt, lt);
 }
 
 // Pass 1 over the plan's tiles (rows = (layer, head, 256-query block),
@@ -405,7 +406,7 @@ __global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_S
     const int h = (int)((i - Ld.lse_rbase) / nb), b = (int)((i - Ld.lse_rbase) % nb);
     const int q0 = b * kBlockRows;
     const int kend_blk = dm.causal ? min(Ld.n, Ld.n_cache + min(q0 + kBlockRows, Ld.n_chunk)) : Ld.n;
-    segment(Ld, dm, l, h, q0, 0, kend_blk, ((int64_t)l * dm.Hq + h) * dm.qb + b, 0, kt0, kt1, sr, part);
+    segment(Ld, dm, l, h, q0, 0, kend_blk, (int64_t)i, kt0, kt1, sr, part);
     return;
   }
   bool first = true;
@@ -429,8 +430,8 @@ __global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_S
       const int q0 = b * kBlockRows;
       const int kend_blk = dm.causal ? min(Ld.n, Ld.n_cache + min(q0 + kBlockRows, Ld.n_chunk)) : Ld.n;
       if (!first) __syncthreads();  // every wave is done with the stages of the previous segment
-      segment(Ld, dm, l, h, q0, ta * kTile, min(tb * kTile, kend_blk), ((int64_t)l * dm.Hq + h) * dm.qb + b,
-              plan_seg(pl, g - ta, g), kt0, kt1, sr, part);
+      segment(Ld, dm, l, h, q0, ta * kTile, min(tb * kTile, kend_blk),
+              plan_slot(pl, Ld.lse_rbase, h, Ld.n_chunk, b) + plan_seg(pl, g - ta, g), kt0, kt1, sr, part);
       g += tb - ta;
       ta = 0;
       if (++b * kBlockRows >= Ld.n_chunk) {
@@ -468,16 +469,18 @@ __global__ __launch_bounds__(256) void lse_merge(const LayerDesc* __restrict__ l
   for (int bb = 0; bb < b; ++bb) start += lse_row_tiles(Ld.n, Ld.n_cache, Ld.n_chunk, bb, dm.causal);
   const int tiles = lse_row_tiles(Ld.n, Ld.n_cache, Ld.n_chunk, b, dm.causal);
   const int nseg = plan_seg(pl, start, start + tiles - 1) + 1;
-  const float2* p = part + ((((int64_t)l * dm.Hq + h) * dm.qb + b) * kMaxSeg) * kBlockRows + (i - b * kBlockRows);
-  float2 v[kMaxSeg];  // all partials requested before the first is used
-#pragma unroll
-  for (int sg = 0; sg < kMaxSeg; ++sg) v[sg] = sg < nseg ? p[sg * kBlockRows] : make_float2(-1e30f, 0.0f);
+  const float2* p = part + plan_slot(pl, Ld.lse_rbase, h, Ld.n_chunk, b) * kBlockRows + (i - b * kBlockRows);
   float mx = -1e30f, sum = 0.0f;
+  for (int s0 = 0; s0 < nseg; s0 += kSegsAtOnce) {
+    float2 v[kSegsAtOnce];  // all requested before the first is used
 #pragma unroll
-  for (int sg = 0; sg < kMaxSeg; ++sg) {
-    const float m2 = fmaxf(mx, v[sg].x);
-    sum = sum * __builtin_amdgcn_exp2f(mx - m2) + v[sg].y * __builtin_amdgcn_exp2f(v[sg].x - m2);
-    mx = m2;
+    for (int u = 0; u < kSegsAtOnce; ++u) v[u] = s0 + u < nseg ? p[(s0 + u) * kBlockRows] : make_float2(-1e30f, 0.0f);
+#pragma unroll
+    for (int u = 0; u < kSegsAtOnce; ++u) {
+      const float m2 = fmaxf(mx, v[u].x);
+      sum = sum * __builtin_amdgcn_exp2f(mx - m2) + v[u].y * __builtin_amdgcn_exp2f(v[u].x - m2);
+      mx = m2;
+    }
   }
   const float v2 = mx + __log2f(sum);
   lse2[o] = v2;
@@ -578,7 +581,7 @@ __device__ inline void colsum_phase(floatx16 (&out)[2], const T* lds, int row, i
 // half executes; query tiles arrive by DMA one tile ahead.
 template <int D>
 __device__ inline void colsum_segment(const LayerDesc& Ld, const Dims& dm, int l, int h, int k0, int qstart,
-                                      int C, int64_t row, int seg, uint16_t* qt0, uint16_t* qt1,
+                                      int C, int64_t pslot, uint16_t* qt0, uint16_t* qt1,
                                       float (&lse2)[3][kTile], const SplitRows&, const float* __restrict__ lse2_all,
                                       float* __restrict__ part) {
   using T = uint16_t;
@@ -700,14 +703,14 @@ __device__ inline void colsum_segment(const LayerDesc& Ld, const Dims& dm, int l
   cs[0] += wave_xor32(cs[0]);
   cs[1] += wave_xor32(cs[1]);
   const int key = kw + half * 32 + (lane & 31);
-  if (key < N) part[(row * kMaxSeg + seg) * kBlockRows + (key - k0)] = half ? cs[1] : cs[0];
+  if (key < N) part[pslot * kBlockRows + (key - k0)] = half ? cs[1] : cs[0];
 }
 
 // The same for fp32 rows, as three-part products: eight wavefronts keep 32
 // keys each.
 template <int D>
 __device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, int l, int h, int k0, int qstart,
-                                          int C, int64_t row, int seg, uint16_t* qt0, uint16_t* qt1,
+                                          int C, int64_t pslot, uint16_t* qt0, uint16_t* qt1,
                                           float (&lse2)[3][kTile], const SplitRows& sr,
                                           const float* __restrict__ lse2_all, float* __restrict__ part) {
   using Tl = SplitTile<D>;
@@ -765,7 +768,7 @@ __device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, i
   if (!active) return;
   const float t = cs[0] + wave_xor32(cs[0]);
   const int key = kw + (lane & 31);
-  if (half == 0 && key < N) part[(row * kMaxSeg + seg) * kBlockRows + (key - k0)] = t;
+  if (half == 0 && key < N) part[pslot * kBlockRows + (key - k0)] = t;
 }
 
 // Pass 2 over the plan's tiles (rows = (layer, head, 256-key block), tiles
@@ -798,8 +801,7 @@ __global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_S
     const int nb = (Ld.n + kBlockRows - 1) / kBlockRows;
     const int h = (int)((i - Ld.cs_rbase) / nb), b = (int)((i - Ld.cs_rbase) % nb);
     const int t0 = cs_first_tile(Ld.n_cache, b, dm.causal);
-    segment(Ld, dm, l, h, b * kBlockRows, t0 * kTile, Ld.n_chunk, ((int64_t)l * dm.Hq + h) * dm.kb + b, 0, qt0, qt1,
-            lse2, sr, lse2_all, part);
+    segment(Ld, dm, l, h, b * kBlockRows, t0 * kTile, Ld.n_chunk, i, qt0, qt1, lse2, sr, lse2_all, part);
     return;
   }
   bool first = true;
@@ -822,7 +824,7 @@ __global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_S
       const int t0 = cs_first_tile(Ld.n_cache, b, dm.causal);
       if (!first) __syncthreads();  // every wave is done with the stages of the previous segment
       segment(Ld, dm, l, h, b * kBlockRows, (t0 + ta) * kTile, min(Ld.n_chunk, (t0 + tb) * kTile),
-              ((int64_t)l * dm.Hq + h) * dm.kb + b, plan_seg(pl, g - ta, g), qt0, qt1, lse2, sr, lse2_all, part);
+              plan_slot(pl, Ld.cs_rbase, h, Ld.n, b) + plan_seg(pl, g - ta, g), qt0, qt1, lse2, sr, lse2_all, part);
       g += tb - ta;
       ta = 0;
       if (++b * kBlockRows >= Ld.n) {
@@ -856,21 +858,28 @@ __global__ void head_sum(const LayerDesc* __restrict__ layers, Dims dm, PassPlan
     // once, then added in head and segment order
     constexpr int kHeadsAtOnce = 8;
     for (int h0 = 0; h0 < dm.G; h0 += kHeadsAtOnce) {
-      float v[kHeadsAtOnce][kMaxSeg];
+      int nseg[kHeadsAtOnce], most = 0;
 #pragma unroll
       for (int u = 0; u < kHeadsAtOnce; ++u) {
-        const int h = g * dm.G + min(h0 + u, dm.G - 1);  // (heads past G load nothing)
-        const int64_t s0 = start + (int64_t)h * Ld.cs_th;
-        const int nseg = h0 + u < dm.G ? plan_seg(pl, s0, s0 + tiles - 1) + 1 : 0;
-        const float* p =
-            part + ((((int64_t)l * dm.Hq + h) * dm.kb + b) * kMaxSeg) * kBlockRows + (j - b * kBlockRows);
-#pragma unroll
-        for (int sg = 0; sg < kMaxSeg; ++sg) v[u][sg] = sg < nseg ? p[sg * kBlockRows] : 0.0f;
+        const int64_t s0 = start + (int64_t)(g * dm.G + h0 + u) * Ld.cs_th;
+        nseg[u] = h0 + u < dm.G ? plan_seg(pl, s0, s0 + tiles - 1) + 1 : 0;  // (heads past G load nothing)
+        most = max(most, nseg[u]);
       }
+      for (int c0 = 0; c0 < most; c0 += kSegsAtOnce) {
+        float v[kHeadsAtOnce][kSegsAtOnce];
 #pragma unroll
-      for (int u = 0; u < kHeadsAtOnce; ++u)
+        for (int u = 0; u < kHeadsAtOnce; ++u) {
+          const int h = g * dm.G + min(h0 + u, dm.G - 1);
+          const float* p =
+              part + (plan_slot(pl, Ld.cs_rbase, h, Ld.n, b) + c0) * kBlockRows + (j - b * kBlockRows);
 #pragma unroll
-        for (int sg = 0; sg < kMaxSeg; ++sg) sum += v[u][sg];
+          for (int sg = 0; sg < kSegsAtOnce; ++sg) v[u][sg] = c0 + sg < nseg[u] ? p[sg * kBlockRows] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kHeadsAtOnce; ++u)
+#pragma unroll
+          for (int sg = 0; sg < kSegsAtOnce; ++sg) sum += v[u][sg];
+      }
     }
   }
   a[((int64_t)l * dm.Hkv + g) * dm.max_tokens + j] = sum;
@@ -928,20 +937,24 @@ void launch_typed(const Dims& dm, const LayerDesc* desc, const Workspace& ws, co
 // Plan a pass of W tiles in `rows` rows, the longest of t_max tiles.  With
 // rows to spare (at least 8 per workgroup slot) the hardware dispatcher
 // balances one workgroup per row best.  Otherwise chunks hold at least
-// t_max / (kMaxSeg - 1) tiles (the bound on segments per row) and, if the
+// t_max / (segs - 1) tiles (segs: the segments a row may have) and, if the
 // work allows, about two rows (a segment's start costs about as much as a
 // few tiles); then as many rounds of P chunks as fit, with the chunk size
-// that fills the rounds evenly.
-PassPlan choose_plan(int64_t W, int64_t rows, int t_max, int max_workgroups) {
-  PassPlan p{W, 0, 1};
+// that fills the rounds evenly.  Work below a chunk of one tile per slot is
+// not kept together: chunks of at least two or four tiles were slower wherever they
+// left slots idle (8 heads, 400 + 200 rows: 21.4, 27.9 and 37.1 us with one, two
+// and four) and no faster elsewhere.
+PassPlan choose_plan(int64_t W, int64_t rows, int t_max, int segs, int max_workgroups) {
+  PassPlan p{W, 0, 1, segs};
   if (W <= 0) return p;
   if (rows >= 8 * (int64_t)max_workgroups && rows < (int64_t{1} << 31) / 2) {
     p.W = rows;
     p.P = (int)xcd_grid(rows);
     p.c = 0;
+    p.segs = 1;
     return p;
   }
-  const int64_t c_min = std::max<int64_t>((t_max + kMaxSeg - 2) / (kMaxSeg - 1), 1);
+  const int64_t c_min = std::max<int64_t>((t_max + segs - 2) / (segs - 1), 1);
   const int64_t c_pref = std::max<int64_t>(c_min, std::max(2 * t_max, 32));
   if (W <= (int64_t)max_workgroups * c_pref) {
     p.P = (int)std::max<int64_t>(1, std::min<int64_t>(max_workgroups, W / c_min));
@@ -989,8 +1002,8 @@ void plan_score(const Dims& dm, LayerDesc* layers, int max_workgroups, PassPlan*
     cs_w += (int64_t)dm.Hq * ch;
     cs_rows += ch > 0 ? (int64_t)dm.Hq * nb : 0;
   }
-  *lse_plan = choose_plan(lse_w, lse_rows, lse_tmax, max_workgroups);
-  *cs_plan = choose_plan(cs_w, cs_rows, cs_tmax, max_workgroups);
+  *lse_plan = choose_plan(lse_w, lse_rows, lse_tmax, plan_segs((int64_t)dm.L * dm.Hq * dm.qb, lse_rows), max_workgroups);
+  *cs_plan = choose_plan(cs_w, cs_rows, cs_tmax, plan_segs((int64_t)dm.L * dm.Hq * dm.kb, cs_rows), max_workgroups);
 }
 
 hipError_t launch_score(const Dims& dm, int dtype, const LayerDesc* desc, const Workspace& ws,
