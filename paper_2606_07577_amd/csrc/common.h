@@ -445,22 +445,33 @@ __device__ inline void pin(V& v) { asm volatile("" : "+v"(v)); }
 
 
 // ---------------------------------------------------------------------------
-// fp32 products on the bf16 matrix cores.  An fp32 value is the exact sum of
-// three bf16 values (its leading 8, middle 8 and last 8 significand bits, cut
-// off, not rounded), so a product of two is nine bf16 products; the three
-// below 2^-24 of the whole are left out, about what one fp32 rounding of the
-// product is worth, and the other six are added in fp32 by the MFMA.  Six
-// 32x32x16 bf16 MFMAs (32 cycles each) replace eight 32x32x2 fp32 ones (64
-// cycles each).  Rows are kept as [D leading | D middle | D last] bf16.
+// fp32 products on the bf16 matrix cores.  An fp32 value x is the exact sum
+// of three bf16 values: x rounded to nearest, the rest rounded to nearest,
+// and what is left (at most 2^-8 and 2^-17 of the power of two at or below
+// |x|, of either sign).  A product of two values is nine bf16 products; six
+// of them are added in fp32 by the MFMA.  The three left out (a middle part
+// with a last part, twice, and the last parts) are together below 1.01 2^-24 of the
+// product of the two powers of two, of either sign: their sum over a row has
+// no bias.  (Parts cut off instead of rounded all have x's sign, and the same
+// three products take up to 2^-21 off every product.)  Six 32x32x16 bf16
+// MFMAs (32 cycles each) replace eight 32x32x2 fp32 ones (64 cycles each).
+// Error of a dot product of 128 terms over the norms, rms and largest of
+// 16384 against 64 bits, in 2^-24, the fp32 MFMA and this: N(0, 1) rows 0.31 and
+// 2.1, 0.10 and 1.0; a row with a near copy of itself 2.7 and 12.4, 1.1 and
+// 4.4; one channel a million times the others, the first one 4.8 and 22, 2.0
+// and 8.9, the last one 0.60 and 2.2, 1.08 and 5.5 (the one order where the
+// fp32 MFMA is the closer: it adds two products at a time, the bf16 MFMA cuts the smaller
+// ones of sixteen near the last place of the largest).
+// Rows are kept as [D leading | D middle | D last] bf16.
 // ---------------------------------------------------------------------------
+__device__ inline uint32_t round_bf16(uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u; }
 __device__ inline void split3(float x, uint32_t (&part)[3]) {
-  const uint32_t u = __float_as_uint(x);
-  part[0] = u >> 16;
-  // (infinities and NaN have no rest)
-  const float r1 = (u & 0x7F800000u) == 0x7F800000u ? 0.0f : x - __uint_as_float(u & 0xFFFF0000u);
-  const uint32_t u1 = __float_as_uint(r1);
-  part[1] = u1 >> 16;
-  part[2] = __float_as_uint(r1 - __uint_as_float(u1 & 0xFFFF0000u)) >> 16;
+  const uint32_t h = round_bf16(__float_as_uint(x));
+  const float r1 = x - __uint_as_float(h);
+  const uint32_t m = round_bf16(__float_as_uint(r1));
+  part[0] = h >> 16;
+  part[1] = m >> 16;
+  part[2] = __float_as_uint(r1 - __uint_as_float(m)) >> 16;
 }
 
 // Four fp32 elements to their places in a split row (dst: the first one's
@@ -521,8 +532,8 @@ struct SplitTile {  // an LDS stage of kScoreTile such rows
   }
   // One 32-row block of a stage against a register block.  The products with
   // a middle or last part of every k-step come first, while the sum is small
-  // (below 2^-7 of the whole) and so are its roundings, then the leading
-  // parts' products; the leading fragments are read from LDS again for them.
+  // (each is at most 2^-8 of its whole product, of either sign) and so are its roundings, then
+  // the leading parts' products; the leading fragments are read from LDS again for them.
   __device__ static inline floatx16 mma(const uint16_t* lds, int r, int half, const bf16x8 (&b)[NKS][3]) {
     floatx16 acc = floatx16{};
 #pragma unroll
