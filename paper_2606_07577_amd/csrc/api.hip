@@ -546,7 +546,9 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
       (c.dtype != OMNIMEM_BF16 &&  // fp32 rows are split for the matrix cores; the Gram pass's in segment order
        ((e = dalloc(ctx, &ws.perm, L * Hkv * T * 3 * (size_t)c.head_dim)) != hipSuccess ||
         (e = dalloc(ctx, &ws.split_q, L * Hq * Cm * 3 * (size_t)c.head_dim)) != hipSuccess ||
-        (e = dalloc(ctx, &ws.split_k, L * Hkv * T * 3 * (size_t)c.head_dim)) != hipSuccess)) ||
+        (e = dalloc(ctx, &ws.split_k, L * Hkv * T * 3 * (size_t)c.head_dim)) != hipSuccess ||
+        (e = dalloc(ctx, &ws.odd_q, L * Hq * (size_t)odd_stride(Cm))) != hipSuccess ||
+        (e = dalloc(ctx, &ws.odd_kv, L * Hkv * (size_t)odd_stride(T))) != hipSuccess)) ||
       (e = dalloc(ctx, &ws.stat_part, L * Hkv * (size_t)allocate_part_chunks(dm) * 2 * 4)) != hipSuccess ||
       (e = dalloc(ctx, &ws.calib, L)) != hipSuccess ||
       (e = dalloc(ctx, &ws.eff, L * 2)) != hipSuccess ||

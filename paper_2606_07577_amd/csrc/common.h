@@ -253,6 +253,8 @@ struct Workspace {
   uint16_t* perm;         // fp32 only: [L][Hkv][max_tokens][3 d] split rows in segment order (visual, then audio)
   uint16_t* split_q;      // fp32 only: [L][Hq][max_chunk][3 d] split queries (see SplitTile)
   uint16_t* split_k;      // fp32 only: [L][Hkv][max_tokens][3 d] split keys
+  uint8_t* odd_q;         // fp32 only: [L][Hq][odd_stride(max_chunk)] flags of split_rows
+  uint8_t* odd_kv;        // fp32 only: [L][Hkv][odd_stride(max_tokens)] of split_rows or lists_norms
   int gram_grid;          // persistent Gram workgroups
   double* stat_part;      // [L][Hkv][chunks][2][4]
   double* calib;          // [L] sums of C^(l) over the calibration steps
@@ -474,9 +476,16 @@ __device__ inline void split3(float x, uint32_t (&part)[3]) {
   part[2] = __float_as_uint(r1 - __uint_as_float(m)) >> 16;
 }
 
+// Whether the parts serve a value (given as its bits): 0, or a magnitude in
+// [2^-50, 2^60).  Then the lowest bit of a product that counts stays above
+// the smallest normal number, and no rounded part or sum of 128 products passes the largest
+// one.  Blocks of rows with any other value (a product of an infinity with
+// another's zero part would be NaN) are multiplied as fp32 (mma_f32).
+__device__ inline bool splittable(uint32_t u) { return (u << 1) == 0 || ((u >> 23) & 0xFFu) - 77u < 110u; }
+
 // Four fp32 elements to their places in a split row (dst: the first one's
-// leading part; the parts are D elements apart).
-__device__ inline void store_split(uint16_t* dst, int D, const uint4& v) {
+// leading part; the parts are D elements apart).  Returns whether the parts serve all four.
+__device__ inline bool store_split(uint16_t* dst, int D, const uint4& v) {
   uint32_t a[4][3];
   split3(__uint_as_float(v.x), a[0]);
   split3(__uint_as_float(v.y), a[1]);
@@ -485,6 +494,32 @@ __device__ inline void store_split(uint16_t* dst, int D, const uint4& v) {
 #pragma unroll
   for (int p = 0; p < 3; ++p)
     *reinterpret_cast<uint2*>(dst + p * D) = make_uint2(a[0][p] | (a[1][p] << 16), a[2][p] | (a[3][p] << 16));
+  return splittable(v.x) && splittable(v.y) && splittable(v.z) && splittable(v.w);
+}
+
+// The kernels that split rows flag, per workgroup and head, whether it met a
+// value that the parts do not serve: in odd[0 .. ceil(rows / kSplitRows)).
+constexpr int kSplitRows = kScoreTile;  // rows per workgroup of split_rows
+__host__ __device__ inline int64_t odd_stride(int64_t rows) { return (rows + kSplitRows - 1) / kSplitRows; }
+// Any flag of [i0, i1) set?  The same in every lane of a wavefront.
+__device__ inline bool any_odd(const uint8_t* odd, int i0, int i1) {
+  int v = 0;
+  for (int i = i0 + (int)(threadIdx.x & 63); i < i1; i += 64) v |= gload<uint8_t>(odd + i);
+  return __any(v);
+}
+
+// A 32x32 block of products of fp32 rows in memory, by the fp32 MFMA: this
+// lane's row x of the output's rows and row y of its columns.
+template <int D>
+__device__ inline floatx16 mma_f32(const float* x, const float* y, int half) {
+  floatx16 acc = floatx16{};
+#pragma unroll 2
+  for (int j = 0; j < D / 8; ++j) {
+    const floatx4 a = gload<floatx4>(x + 8 * j + 4 * half), b = gload<floatx4>(y + 8 * j + 4 * half);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = Mfma<float>::mma(a[e], b[e], acc);
+  }
+  return acc;
 }
 
 template <int D>

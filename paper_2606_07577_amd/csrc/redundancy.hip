@@ -116,7 +116,8 @@ constexpr int kListRows = 128;
 template <typename T, int D, bool PERM>
 __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__ layers, Dims dm, int on_keys,
                                                    int* __restrict__ pos, int* __restrict__ counts, uint16_t* __restrict__ perm,
-                                                   float* __restrict__ inv, int* __restrict__ best) {
+                                                   uint8_t* __restrict__ odd, float* __restrict__ inv,
+                                                   int* __restrict__ best) {
   const int l = blockIdx.z, g = blockIdx.y;
   const LayerDesc Ld = layers[l];
   const int N = Ld.n;
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__
   static_assert(NP <= LPR, "a lane of the group for every pass");
   double mine = 0.0;
   int64_t omine = 0;
-  bool in_mine = false;
+  bool in_mine = false, served = true;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const int r = p * RPP + (int)threadIdx.x / LPR;
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__
     int64_t o = 0;
     if (in) {
       o = ((int64_t)l * dm.Hkv + g) * dm.max_tokens + dst[r];
-      if constexpr (PERM) store_split(perm + o * 3 * D + sub * EPL, D, v[p]);
+      if constexpr (PERM) served &= store_split(perm + o * 3 * D + sub * EPL, D, v[p]);
       const uint32_t w[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -256,11 +257,15 @@ __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__
     inv[omine] = mine > 0.0 ? (float)(1.0 / sqrt(mine)) : 0.0f;
     best[omine] = kNoPartner;  // the Gram pass merges maxima into this
   }
+  if constexpr (PERM) {
+    const int any = __syncthreads_or(!served);
+    if (threadIdx.x == 0) odd[((int64_t)l * dm.Hkv + g) * odd_stride(dm.max_tokens) + blockIdx.x] = any ? 1 : 0;
+  }
 }
 
 // --- Gram max ------------------------------------------------------------------
 // fp32 rows, as three-part products (SplitTile) over a copy of the rows in
-// list order.
+// list order; a head with a value that the parts do not serve, from the rows themselves as fp32.
 // Work layout: a "row" is one block of 256 segment rows (8 waves x 32) held
 // as MFMA B operands in registers; its "tiles" are all 64-row tiles of the
 // same segment, streamed through LDS by DMA as A operands.  Rows of all
@@ -287,7 +292,8 @@ __device__ inline int64_t gram_seg_tiles(int K) {
 
 template <int D, bool BY_XCD>
 __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_pass(
-    const LayerDesc* __restrict__ layers, Dims dm, const int* __restrict__ counts, const uint16_t* __restrict__ perm,
+    const LayerDesc* __restrict__ layers, Dims dm, int on_keys, const int* __restrict__ counts,
+    const int* __restrict__ pos, const uint16_t* __restrict__ perm, const uint8_t* __restrict__ odd_rows,
     const float* __restrict__ inv, int* __restrict__ best) {
   using Tl = SplitTile<D>;
   constexpr int kMaxL = 1024;
@@ -374,6 +380,8 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_pass(
       const float my_inv = gload<float>(invs + my);
       bf16x8 bf[Tl::NKS][3];
       Tl::gload_all(bf, U + (int64_t)my * Tl::ROW, half);
+      const bool odd = any_odd(odd_rows + ((int64_t)l * dm.Hkv + g) * odd_stride(dm.max_tokens), 0,
+                               (kv + ka + kListRows - 1) / kListRows);
       float rmax = -INFINITY;
       auto step = [&](int t, int st, const uint16_t* cur, uint16_t* nxt) {
         if (threadIdx.x < kScoreTile) jinv[st][threadIdx.x] = t > t0 ? jinv_next : jinv_first;
@@ -385,7 +393,17 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_pass(
         }
         floatx16 acc[2];
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) acc[rb] = Tl::mma(cur, rb * 32 + (lane & 31), half, bf);
+        for (int rb = 0; rb < 2; ++rb) {
+          if (odd) {
+            const LayerDesc& Ld = layers[l];
+            const float* u = reinterpret_cast<const float*>(on_keys ? Ld.k : Ld.v) + (int64_t)g * Ld.kv_hs;
+            const int* P = pos + (int64_t)(2 * l + mu) * list_stride(dm.max_tokens);
+            const int at = min(t * kScoreTile + rb * 32 + (lane & 31), K - 1);
+            acc[rb] = mma_f32<D>(u + (int64_t)gload<int>(P + at) * Ld.kv_rs, u + (int64_t)gload<int>(P + my) * Ld.kv_rs, half);
+          } else {
+            acc[rb] = Tl::mma(cur, rb * 32 + (lane & 31), half, bf);
+          }
+        }
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
           float ij[16];
@@ -1241,7 +1259,7 @@ void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, c
   if constexpr (sizeof(T) == 2) {  // bf16: each pair once, rows gathered through the row lists
     OMNIMEM_LAUNCH(ws, K_NORMS, st,
                    lists_norms<T, D, false><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts,
-                                                                   perm, ws.inv_norm, ws.best));
+                                                                   perm, ws.odd_kv, ws.inv_norm, ws.best));
     OMNIMEM_LAUNCH(ws, K_GRAM_SYM, st,
                    gram_sym<D><<<ws.gram_grid, 256, 0, st>>>(desc, dm, on_keys, ws.counts, ws.pos, ws.inv_norm, ws.best));
     OMNIMEM_LAUNCH(ws, K_GRAM_FINISH, st, gram_finish<<<gtok, 256, 0, st>>>(desc, dm, ws.pos, ws.counts, ws.best, s));
@@ -1249,14 +1267,16 @@ void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, c
   }
   OMNIMEM_LAUNCH(ws, K_NORMS, st,
                  lists_norms<T, D, true><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, perm,
-                                                                ws.inv_norm, ws.best));
+                                                                ws.odd_kv, ws.inv_norm, ws.best));
   const bool by_xcd = dm.L * dm.Hkv >= 2 * kXcds && ws.gram_grid % kXcds == 0;
   if (by_xcd)
     OMNIMEM_LAUNCH(ws, K_GRAM, st,
-                   gram_pass<D, true><<<ws.gram_grid, 64 * kGramWaves, 0, st>>>(desc, dm, ws.counts, perm, ws.inv_norm, ws.best));
+                   gram_pass<D, true><<<ws.gram_grid, 64 * kGramWaves, 0, st>>>(desc, dm, on_keys, ws.counts, ws.pos, perm,
+                                                                               ws.odd_kv, ws.inv_norm, ws.best));
   else
     OMNIMEM_LAUNCH(ws, K_GRAM, st,
-                   gram_pass<D, false><<<ws.gram_grid, 64 * kGramWaves, 0, st>>>(desc, dm, ws.counts, perm, ws.inv_norm, ws.best));
+                   gram_pass<D, false><<<ws.gram_grid, 64 * kGramWaves, 0, st>>>(desc, dm, on_keys, ws.counts, ws.pos, perm,
+                                                                               ws.odd_kv, ws.inv_norm, ws.best));
   OMNIMEM_LAUNCH(ws, K_GRAM_FINISH, st, gram_finish<<<gtok, 256, 0, st>>>(desc, dm, ws.pos, ws.counts, ws.best, s));
 }
 

@@ -88,9 +88,10 @@ __device__ inline void online_update(const floatx16& acc, float sl2, float& m, f
 struct SplitRows {
   const uint16_t* q;  // [L][Hq][max_chunk][3 D]
   const uint16_t* k;  // [L][Hkv][max_tokens][3 D]
+  const uint8_t* odd_q;
+  const uint8_t* odd_k;
 };
 constexpr int kSplitWaves = 8;
-constexpr int kSplitRows = 64;  // rows per workgroup of split_rows
 static_assert(kBlockRows == 32 * kSplitWaves, "32 rows per wavefront");
 
 // Stage elements and workgroup of a pass.
@@ -325,7 +326,8 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int, int
 // 16.  2 layers x 16 heads, 1024 queries, 3072 + 1024 keys of width 64: 104 us
 // (234 us with the 32x32x2 fp32 MFMA), the column sums 86 us (174 us); one
 // layer x 28 heads, 1500 queries, 4500 keys of width 128: 243 us (516 us, with
-// 123 registers spilled) and 242 us (504 us).
+// 123 registers spilled) and 242 us (504 us).  A segment with a value that the parts do not serve
+// is multiplied as fp32, from the rows themselves.
 template <int D>
 __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int l, int h, int q0, int kr0, int kr1,
                                        int64_t pslot, uint16_t* kt0, uint16_t* kt1, const SplitRows& sr,
@@ -343,10 +345,14 @@ __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int 
   copy(kt0, kr0);
   bf16x8 qf[Tl::NKS][3];
   Tl::gload_all(qf, q + (int64_t)min(qw + (lane & 31), C - 1) * Tl::ROW, half);
+  // (the workgroup's rows and keys: every wave finds the same)
+  const bool odd = any_odd(sr.odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk), q0 / kSplitRows,
+                           (min(q0 + kBlockRows, C) + kSplitRows - 1) / kSplitRows) ||
+                   any_odd(sr.odd_k + ((int64_t)l * dm.Hkv + h / dm.G) * odd_stride(dm.max_tokens), kr0 / kSplitRows,
+                           (kr1 + kSplitRows - 1) / kSplitRows);
   const float sl2 = Ld.scale_log2;
   float m = -1e30f, lsum = 0.0f;
-  auto scores = [&](const uint16_t* lds, int kb, int rb) {
-    floatx16 acc = Tl::mma(lds, rb * 32 + (lane & 31), half, qf);
+  auto mask = [&](floatx16& acc, int kb) {
     if (kb + 32 > kend_wave || (dm.causal && kb + 31 - nc > qw)) {
       const int base = kb + half * 4;
       int lim = kend_wave - 1 - base;
@@ -354,20 +360,34 @@ __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = (r >> 2) * 8 + (r & 3) <= lim ? acc[r] : -INFINITY;
     }
-    return acc;
   };
   auto step = [&](int t, uint16_t* cur, uint16_t* nxt) {
     dma_wait();
     __syncthreads();  // tile t landed; every wave is done with the other stage
     if (t + kTile < kr1) copy(nxt, t + kTile);
     if (!active || t >= kend_wave) return;
-    const floatx16 a0 = scores(cur, t, 0), a1 = scores(cur, t + 32, 1);
+    floatx16 a0 = Tl::mma(cur, lane & 31, half, qf);
+    mask(a0, t);
+    floatx16 a1 = Tl::mma(cur, 32 + (lane & 31), half, qf);
+    mask(a1, t + 32);
     online_update(a0, sl2, m, lsum);
     online_update(a1, sl2, m, lsum);
   };
-  for (int t = kr0; t < kr1; t += 2 * kTile) {
-    step(t, kt0, kt1);
-    if (t + kTile < kr1) step(t + kTile, kt1, kt0);
+  if (odd) {
+    const float* q32 = reinterpret_cast<const float*>(Ld.q) + (int64_t)h * Ld.q_hs;
+    const float* k32 = reinterpret_cast<const float*>(Ld.k) + (int64_t)(h / dm.G) * Ld.kv_hs;
+    for (int t = kr0; active && t < kend_wave; t += 32) {
+      floatx16 acc = mma_f32<D>(k32 + (int64_t)min(t + (lane & 31), N - 1) * Ld.kv_rs,
+                                q32 + (int64_t)min(qw + (lane & 31), C - 1) * Ld.q_rs, half);
+      mask(acc, t);
+      online_update(acc, sl2, m, lsum);
+    }
+    dma_wait();
+  } else {
+    for (int t = kr0; t < kr1; t += 2 * kTile) {
+      step(t, kt0, kt1);
+      if (t + kTile < kr1) step(t + kTile, kt1, kt0);
+    }
   }
   if (!active) return;
   const float m2 = wave_xor32(m), l2 = wave_xor32(lsum);
@@ -736,8 +756,19 @@ __device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, i
   }
   bf16x8 kf[Tl::NKS][3];
   Tl::gload_all(kf, k + (int64_t)min(kw + (lane & 31), N - 1) * Tl::ROW, half);
+  const bool odd = any_odd(sr.odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk), qstart / kSplitRows,
+                           (C + kSplitRows - 1) / kSplitRows) ||
+                   any_odd(sr.odd_k + ((int64_t)l * dm.Hkv + h / dm.G) * odd_stride(dm.max_tokens), k0 / kSplitRows,
+                           (min(k0 + kBlockRows, N) + kSplitRows - 1) / kSplitRows);
   const float sl2 = Ld.scale_log2;
   float cs[1] = {0.0f};
+  auto mask = [&](floatx16& acc, int qb) {
+    if (dm.causal && kw + 31 - nc > qb) {
+      const int dlim = kw + (lane & 31) - nc - qb - half * 4;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = ((r >> 2) * 8 + (r & 3)) >= dlim ? acc[r] : -INFINITY;
+    }
+  };
   auto step = [&](int qt, int i, uint16_t* cur, uint16_t* nxt) {
     if (threadIdx.x < kTile) lse2[i][threadIdx.x] = lse_next;
     dma_wait();
@@ -751,19 +782,34 @@ __device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, i
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       acc[rb][0] = Tl::mma(cur, rb * 32 + (lane & 31), half, kf);
-      const int qb = qt + rb * 32;
-      if (dm.causal && kw + 31 - nc > qb) {
-        const int dlim = kw + (lane & 31) - nc - qb - half * 4;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[rb][0][r] = ((r >> 2) * 8 + (r & 3)) >= dlim ? acc[rb][0][r] : -INFINITY;
-      }
+      mask(acc[rb][0], qt + rb * 32);
     }
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) colsum_update(acc[rb], &lse2[i][rb * 32], half, sl2, cs);
   };
-  for (int qt = qstart; qt < C; qt += 2 * kTile) {
-    step(qt, 0, qt0, qt1);
-    if (qt + kTile < C) step(qt + kTile, 1, qt1, qt0);
+  if (odd) {
+    const float* q32 = reinterpret_cast<const float*>(Ld.q) + (int64_t)h * Ld.q_hs;
+    const float* k32 = reinterpret_cast<const float*>(Ld.k) + (int64_t)(h / dm.G) * Ld.kv_hs;
+    for (int qt = qstart, i = 0; qt < C; qt += kTile, i ^= 1) {
+      if (threadIdx.x < kTile) lse2[i][threadIdx.x] = lse_next;
+      __syncthreads();
+      if (qt + kTile < C) lse_next = load_lse(qt + kTile);
+      if (!active || qt + kTile <= qfirst_wave) continue;
+#pragma unroll 1
+      for (int rb = 0; rb < 2; ++rb) {
+        floatx16 acc[1];
+        acc[0] = mma_f32<D>(q32 + (int64_t)min(qt + rb * 32 + (lane & 31), C - 1) * Ld.q_rs,
+                            k32 + (int64_t)min(kw + (lane & 31), N - 1) * Ld.kv_rs, half);
+        mask(acc[0], qt + rb * 32);
+        colsum_update(acc, &lse2[i][rb * 32], half, sl2, cs);
+      }
+    }
+    dma_wait();
+  } else {
+    for (int qt = qstart; qt < C; qt += 2 * kTile) {
+      step(qt, 0, qt0, qt1);
+      if (qt + kTile < C) step(qt + kTile, 1, qt1, qt0);
+    }
   }
   if (!active) return;
   const float t = cs[0] + wave_xor32(cs[0]);
@@ -886,16 +932,18 @@ __global__ void head_sum(const LayerDesc* __restrict__ layers, Dims dm, PassPlan
 }
 
 // fp32 queries and keys of every layer as three-part rows: four elements per
-// thread, the query heads' rows, then the KV heads'.
+// thread, the query heads' rows, then the KV heads'; and the workgroup's flag.
 template <int D>
 __global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ layers, Dims dm, uint16_t* __restrict__ sq,
-                                                  uint16_t* __restrict__ sk) {
+                                                  uint16_t* __restrict__ sk, uint8_t* __restrict__ odd_q,
+                                                  uint8_t* __restrict__ odd_k) {
   constexpr int TPR = D / 4, RPB = 256 / TPR;  // threads per row, rows per workgroup and step
   const int l = blockIdx.z, head = blockIdx.y;
   const LayerDesc& Ld = layers[l];
   const bool is_q = head < dm.Hq;
   const int h = is_q ? head : head - dm.Hq;
   const int rows = is_q ? Ld.n_chunk : Ld.n;
+  if ((int)blockIdx.x * kSplitRows >= rows) return;  // the whole workgroup
   const float* src = reinterpret_cast<const float*>(is_q ? Ld.q : Ld.k) + (int64_t)h * (is_q ? Ld.q_hs : Ld.kv_hs);
   const int64_t rs = is_q ? Ld.q_rs : Ld.kv_rs;
   uint16_t* dst = is_q ? sq + ((int64_t)l * dm.Hq + h) * dm.max_chunk * 3 * D
@@ -908,21 +956,26 @@ __global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ 
     const int r = (int)blockIdx.x * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
     if (r < rows) v[p] = gload16(src + (int64_t)r * rs + e);
   }
+  bool served = true;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const int r = (int)blockIdx.x * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
-    if (r < rows) store_split(dst + (int64_t)r * 3 * D + e, D, v[p]);
+    if (r < rows) served &= store_split(dst + (int64_t)r * 3 * D + e, D, v[p]);
   }
+  const int odd = __syncthreads_or(!served);
+  if (threadIdx.x == 0)
+    (is_q ? odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk)
+          : odd_k + ((int64_t)l * dm.Hkv + h) * odd_stride(dm.max_tokens))[blockIdx.x] = odd ? 1 : 0;
 }
 
 template <typename T, int D>
 void launch_typed(const Dims& dm, const LayerDesc* desc, const Workspace& ws, const PassPlan& lp,
                   const PassPlan& cp, float* lse_out, float* a, hipStream_t st) {
   constexpr int kTh = PassShape<T, D>::THREADS;
-  const SplitRows sr{ws.split_q, ws.split_k};
+  const SplitRows sr{ws.split_q, ws.split_k, ws.odd_q, ws.odd_kv};
   if constexpr (sizeof(T) == 4) {
     const dim3 gs((unsigned)((std::max(dm.max_tokens, dm.max_chunk) + kSplitRows - 1) / kSplitRows), dm.Hq + dm.Hkv, dm.L);
-    OMNIMEM_LAUNCH(ws, K_SPLIT, st, split_rows<D><<<gs, 256, 0, st>>>(desc, dm, ws.split_q, ws.split_k));
+    OMNIMEM_LAUNCH(ws, K_SPLIT, st, split_rows<D><<<gs, 256, 0, st>>>(desc, dm, ws.split_q, ws.split_k, ws.odd_q, ws.odd_kv));
   }
   if (lp.W > 0)
     OMNIMEM_LAUNCH(ws, K_LSE, st, lse_pass<T, D><<<lp.P, kTh, 0, st>>>(desc, dm, lp, sr, ws.lse_part));
