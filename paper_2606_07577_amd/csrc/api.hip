@@ -543,12 +543,6 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
       (e = dalloc(ctx, &ws.counts, L * 2)) != hipSuccess ||
       (e = dalloc(ctx, &ws.inv_norm, L * Hkv * T)) != hipSuccess ||
       (e = dalloc(ctx, &ws.best, L * Hkv * T)) != hipSuccess ||
-      (c.dtype != OMNIMEM_BF16 &&  // fp32 rows are split for the matrix cores; the Gram pass's in segment order
-       ((e = dalloc(ctx, &ws.perm, L * Hkv * T * 3 * (size_t)c.head_dim)) != hipSuccess ||
-        (e = dalloc(ctx, &ws.split_q, L * Hq * Cm * 3 * (size_t)c.head_dim)) != hipSuccess ||
-        (e = dalloc(ctx, &ws.split_k, L * Hkv * T * 3 * (size_t)c.head_dim)) != hipSuccess ||
-        (e = dalloc(ctx, &ws.odd_q, L * Hq * (size_t)odd_stride(Cm))) != hipSuccess ||
-        (e = dalloc(ctx, &ws.odd_kv, L * Hkv * (size_t)odd_stride(T))) != hipSuccess)) ||
       (e = dalloc(ctx, &ws.stat_part, L * Hkv * (size_t)allocate_part_chunks(dm) * 2 * 4)) != hipSuccess ||
       (e = dalloc(ctx, &ws.calib, L)) != hipSuccess ||
       (e = dalloc(ctx, &ws.eff, L * 2)) != hipSuccess ||
@@ -592,6 +586,20 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
     if ((e = hipEventCreateWithFlags(&ctx->ev[i], hipEventDisableTiming | hipEventDisableSystemFence)) != hipSuccess) {
       omnimem_destroy(ctx);
       return fail(nullptr, OMNIMEM_ERR_HIP, "event: %s", hipGetErrorString(e));
+    }
+  }
+  // fp32 rows as bf16 parts: 1.5 times the bytes of the queries and of one of the caches, last and only if there is
+  // memory for all of it, since the passes can do without (at the fp32 MFMA's speed)
+  if (c.dtype != OMNIMEM_BF16) {
+    const size_t before = ctx->allocations.size();
+    if (dalloc(ctx, &ws.split_kv, L * Hkv * T * 3 * (size_t)c.head_dim) != hipSuccess ||
+        dalloc(ctx, &ws.split_q, L * Hq * Cm * 3 * (size_t)c.head_dim) != hipSuccess ||
+        dalloc(ctx, &ws.odd_q, L * Hq * (size_t)odd_stride(Cm)) != hipSuccess ||
+        dalloc(ctx, &ws.odd_kv, L * Hkv * (size_t)odd_stride(T)) != hipSuccess) {
+      (void)hipGetLastError();
+      for (; ctx->allocations.size() > before; ctx->allocations.pop_back()) (void)hipFree(ctx->allocations.back());
+      ws.split_kv = ws.split_q = nullptr;
+      ws.odd_q = ws.odd_kv = nullptr;
     }
   }
   *out = ctx;

@@ -250,9 +250,10 @@ struct Workspace {
   int* counts;            // [L][2]           K_v, K_a
   float* inv_norm;        // [L][Hkv][max_tokens] inverse norms, segment order
   int* best;              // [L][Hkv][max_tokens] ord_f32 of the best cosine, segment order
-  uint16_t* perm;         // fp32 only: [L][Hkv][max_tokens][3 d] split rows in segment order (visual, then audio)
-  uint16_t* split_q;      // fp32 only: [L][Hq][max_chunk][3 d] split queries (see SplitTile)
-  uint16_t* split_k;      // fp32 only: [L][Hkv][max_tokens][3 d] split keys
+  // fp32 only, null when there was no memory for them (the passes then multiply as fp32):
+  uint16_t* split_q;      // [L][Hq][max_chunk][3 d] split queries (see SplitTile)
+  uint16_t* split_kv;     // [L][Hkv][max_tokens][3 d] a score call's split keys, or a redundancy call's split
+                          // rows in segment order (visual, then audio)
   uint8_t* odd_q;         // fp32 only: [L][Hq][odd_stride(max_chunk)] flags of split_rows
   uint8_t* odd_kv;        // fp32 only: [L][Hkv][odd_stride(max_tokens)] of split_rows or lists_norms
   int gram_grid;          // persistent Gram workgroups
@@ -466,46 +467,56 @@ __device__ inline void pin(V& v) { asm volatile("" : "+v"(v)); }
 // ones of sixteen near the last place of the largest).
 // Rows are kept as [D leading | D middle | D last] bf16.
 // ---------------------------------------------------------------------------
-__device__ inline uint32_t round_bf16(uint32_t u) { return (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u; }
-__device__ inline void split3(float x, uint32_t (&part)[3]) {
-  const uint32_t h = round_bf16(__float_as_uint(x));
-  const float r1 = x - __uint_as_float(h);
-  const uint32_t m = round_bf16(__float_as_uint(r1));
-  part[0] = h >> 16;
-  part[1] = m >> 16;
-  part[2] = __float_as_uint(r1 - __uint_as_float(m)) >> 16;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+// Two values rounded to bf16, as the two halves of a word.
+__device__ inline uint32_t round2(float x, float y) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{x, y}, bf16x2));
+}
+// The three parts of two values.
+__device__ inline void split2(float x, float y, uint32_t (&part)[3]) {
+  part[0] = round2(x, y);
+  const float rx = x - __uint_as_float(part[0] << 16), ry = y - __uint_as_float(part[0] & 0xFFFF0000u);
+  part[1] = round2(rx, ry);
+  part[2] = round2(rx - __uint_as_float(part[1] << 16), ry - __uint_as_float(part[1] & 0xFFFF0000u));
 }
 
-// Whether the parts serve a value (given as its bits): 0, or a magnitude in
-// [2^-50, 2^60).  Then the lowest bit of a product that counts stays above
+// Four fp32 elements to their places in a split row (dst: the first one's
+// leading part; the parts are D elements apart).
+__device__ inline void store_split(uint16_t* dst, int D, const uint4& v) {
+  uint32_t a[3], b[3];
+  split2(__uint_as_float(v.x), __uint_as_float(v.y), a);
+  split2(__uint_as_float(v.z), __uint_as_float(v.w), b);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(dst + p * D) = make_uint2(a[p], b[p]);
+}
+
+// Whether the parts serve values (given as their bits): each 0, or of a
+// magnitude in [2^-50, 2^60).  Then the lowest bit of a product that counts stays above
 // the smallest normal number, and no rounded part or sum of 128 products passes the largest
 // one.  Blocks of rows with any other value (a product of an infinity with
 // another's zero part would be NaN) are multiplied as fp32 (mma_f32).
-__device__ inline bool splittable(uint32_t u) { return (u << 1) == 0 || ((u >> 23) & 0xFFu) - 77u < 110u; }
-
-// Four fp32 elements to their places in a split row (dst: the first one's
-// leading part; the parts are D elements apart).  Returns whether the parts serve all four.
-__device__ inline bool store_split(uint16_t* dst, int D, const uint4& v) {
-  uint32_t a[4][3];
-  split3(__uint_as_float(v.x), a[0]);
-  split3(__uint_as_float(v.y), a[1]);
-  split3(__uint_as_float(v.z), a[2]);
-  split3(__uint_as_float(v.w), a[3]);
-#pragma unroll
-  for (int p = 0; p < 3; ++p)
-    *reinterpret_cast<uint2*>(dst + p * D) = make_uint2(a[0][p] | (a[1][p] << 16), a[2][p] | (a[3][p] << 16));
-  return splittable(v.x) && splittable(v.y) && splittable(v.z) && splittable(v.w);
-}
+struct SplitRange {
+  uint32_t top = 0, low = ~0u;  // largest magnitude; smallest above 0, less 1 (0 counts as the largest word)
+  __device__ inline void add(uint32_t u) {
+    top = max(top, u & 0x7FFFFFFFu);
+    low = min(low, (u & 0x7FFFFFFFu) - 1u);
+  }
+  __device__ inline void add(const uint4& v) {
+    add(v.x); add(v.y); add(v.z); add(v.w);
+  }
+  __device__ inline bool serves() const { return top < ((127u + 60u) << 23) && low >= ((127u - 50u) << 23) - 1u; }
+};
 
 // The kernels that split rows flag, per workgroup and head, whether it met a
 // value that the parts do not serve: in odd[0 .. ceil(rows / kSplitRows)).
 constexpr int kSplitRows = kScoreTile;  // rows per workgroup of split_rows
 __host__ __device__ inline int64_t odd_stride(int64_t rows) { return (rows + kSplitRows - 1) / kSplitRows; }
-// Any flag of [i0, i1) set?  The same in every lane of a wavefront.
-__device__ inline bool any_odd(const uint8_t* odd, int i0, int i1) {
+// This lane's share of the flags [i0, i1) (every wavefront reads them all).
+__device__ inline int odd_flags(const uint8_t* odd, int i0, int i1) {
   int v = 0;
   for (int i = i0 + (int)(threadIdx.x & 63); i < i1; i += 64) v |= gload<uint8_t>(odd + i);
-  return __any(v);
+  return v;
 }
 
 // A 32x32 block of products of fp32 rows in memory, by the fp32 MFMA: this

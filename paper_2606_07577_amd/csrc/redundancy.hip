@@ -223,7 +223,8 @@ __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__
   static_assert(NP <= LPR, "a lane of the group for every pass");
   double mine = 0.0;
   int64_t omine = 0;
-  bool in_mine = false, served = true;
+  bool in_mine = false;
+  SplitRange range;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const int r = p * RPP + (int)threadIdx.x / LPR;
@@ -232,7 +233,10 @@ __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__
     int64_t o = 0;
     if (in) {
       o = ((int64_t)l * dm.Hkv + g) * dm.max_tokens + dst[r];
-      if constexpr (PERM) served &= store_split(perm + o * 3 * D + sub * EPL, D, v[p]);
+      if constexpr (PERM) {
+        store_split(perm + o * 3 * D + sub * EPL, D, v[p]);
+        range.add(v[p]);
+      }
       const uint32_t w[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -258,14 +262,15 @@ __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__
     best[omine] = kNoPartner;  // the Gram pass merges maxima into this
   }
   if constexpr (PERM) {
-    const int any = __syncthreads_or(!served);
+    const int any = __syncthreads_or(!range.serves());
     if (threadIdx.x == 0) odd[((int64_t)l * dm.Hkv + g) * odd_stride(dm.max_tokens) + blockIdx.x] = any ? 1 : 0;
   }
 }
 
 // --- Gram max ------------------------------------------------------------------
 // fp32 rows, as three-part products (SplitTile) over a copy of the rows in
-// list order; a head with a value that the parts do not serve, from the rows themselves as fp32.
+// list order; a head with a value that the parts do not serve, or all heads without memory for the copy (perm null),
+// as fp32 from the rows themselves.
 // Work layout: a "row" is one block of 256 segment rows (8 waves x 32) held
 // as MFMA B operands in registers; its "tiles" are all 64-row tiles of the
 // same segment, streamed through LDS by DMA as A operands.  Rows of all
@@ -367,11 +372,11 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_pass(
       // No load is waited for before the tile loop: the first tile's norms
       // and the register rows' own norms (for the final maxima) are held in
       // registers meanwhile.
-      Tl::template copy<kGramWaves>(jt0, U + (int64_t)t0 * Tl::ELEMS, tile_rows(t0));
+      if (perm) Tl::template copy<kGramWaves>(jt0, U + (int64_t)t0 * Tl::ELEMS, tile_rows(t0));
       const float jinv_first = threadIdx.x < kScoreTile ? jinv_of(t0) : 0.0f;
       float jinv_next = 0.0f;
       if (t0 + 1 < t1) {
-        Tl::template copy<kGramWaves>(jt1, U + (int64_t)(t0 + 1) * Tl::ELEMS, tile_rows(t0 + 1));
+        if (perm) Tl::template copy<kGramWaves>(jt1, U + (int64_t)(t0 + 1) * Tl::ELEMS, tile_rows(t0 + 1));
         if (threadIdx.x < kScoreTile) jinv_next = jinv_of(t0 + 1);
       }
       // this wave's 32 register rows
@@ -379,53 +384,65 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_pass(
       const int my = min(c0 + (lane & 31), K - 1);
       const float my_inv = gload<float>(invs + my);
       bf16x8 bf[Tl::NKS][3];
-      Tl::gload_all(bf, U + (int64_t)my * Tl::ROW, half);
-      const bool odd = any_odd(odd_rows + ((int64_t)l * dm.Hkv + g) * odd_stride(dm.max_tokens), 0,
-                               (kv + ka + kListRows - 1) / kListRows);
+      int flags = 1;
+      if (perm) {
+        flags = odd_flags(odd_rows + ((int64_t)l * dm.Hkv + g) * odd_stride(dm.max_tokens), 0,
+                          (kv + ka + kListRows - 1) / kListRows);
+        Tl::gload_all(bf, U + (int64_t)my * Tl::ROW, half);
+      }
       float rmax = -INFINITY;
+      // the products of 32 tile rows from col0 enter the register rows' maxima
+      auto merge = [&](floatx16& acc, int col0, const float* norms) {
+        float ij[16];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const floatx4 v = *reinterpret_cast<const floatx4*>(norms + j * 8 + half * 4);
+          ij[j * 4 + 0] = v[0]; ij[j * 4 + 1] = v[1]; ij[j * 4 + 2] = v[2]; ij[j * 4 + 3] = v[3];
+        }
+        if (col0 == c0) {  // (blocks of 32 rows are aligned: the pairs of a row with itself)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[r] = acc_row(r, lane) == (lane & 31) ? __builtin_nanf("") : acc[r];
+        }
+        float m = rmax;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) m = fmaxf(m, fmaxf(acc[r] * ij[r], acc[r + 1] * ij[r + 1]));
+        rmax = m;
+      };
       auto step = [&](int t, int st, const uint16_t* cur, uint16_t* nxt) {
         if (threadIdx.x < kScoreTile) jinv[st][threadIdx.x] = t > t0 ? jinv_next : jinv_first;
         dma_wait();
         __syncthreads();  // tile t and its norms landed; tile t-1's stage is free
         if (t > t0 && t + 1 < t1) {
-          Tl::template copy<kGramWaves>(nxt, U + (int64_t)(t + 1) * Tl::ELEMS, tile_rows(t + 1));
+          if (perm) Tl::template copy<kGramWaves>(nxt, U + (int64_t)(t + 1) * Tl::ELEMS, tile_rows(t + 1));
           if (threadIdx.x < kScoreTile) jinv_next = jinv_of(t + 1);
         }
         floatx16 acc[2];
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-          if (odd) {
-            const LayerDesc& Ld = layers[l];
-            const float* u = reinterpret_cast<const float*>(on_keys ? Ld.k : Ld.v) + (int64_t)g * Ld.kv_hs;
-            const int* P = pos + (int64_t)(2 * l + mu) * list_stride(dm.max_tokens);
-            const int at = min(t * kScoreTile + rb * 32 + (lane & 31), K - 1);
-            acc[rb] = mma_f32<D>(u + (int64_t)gload<int>(P + at) * Ld.kv_rs, u + (int64_t)gload<int>(P + my) * Ld.kv_rs, half);
-          } else {
-            acc[rb] = Tl::mma(cur, rb * 32 + (lane & 31), half, bf);
-          }
-        }
+        for (int rb = 0; rb < 2; ++rb) acc[rb] = Tl::mma(cur, rb * 32 + (lane & 31), half, bf);
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-          float ij[16];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const floatx4 v = *reinterpret_cast<const floatx4*>(&jinv[st][rb * 32 + j * 8 + half * 4]);
-            ij[j * 4 + 0] = v[0]; ij[j * 4 + 1] = v[1]; ij[j * 4 + 2] = v[2]; ij[j * 4 + 3] = v[3];
-          }
-          const int col0 = t * kScoreTile + rb * 32;
-          if (col0 == c0) {  // (blocks of 32 rows are aligned: the pairs of a row with itself)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[rb][r] = acc_row(r, lane) == (lane & 31) ? __builtin_nanf("") : acc[rb][r];
-          }
-          float m = rmax;
-#pragma unroll
-          for (int r = 0; r < 16; r += 2) m = fmaxf(m, fmaxf(acc[rb][r] * ij[r], acc[rb][r + 1] * ij[r + 1]));
-          rmax = m;
-        }
+        for (int rb = 0; rb < 2; ++rb) merge(acc[rb], t * kScoreTile + rb * 32, &jinv[st][rb * 32]);
       };
-      for (int t = t0; t < t1; t += 2) {
+      for (int t = t0; perm && t < t1; t += 2) {
         step(t, 0, jt0, jt1);
         if (t + 1 < t1) step(t + 1, 1, jt1, jt0);
+      }
+      if (__any(flags)) {  // again, as fp32 (every wave of the workgroup, or none)
+        const LayerDesc& Ld = layers[l];
+        const float* u = reinterpret_cast<const float*>(on_keys ? Ld.k : Ld.v) + (int64_t)g * Ld.kv_hs;
+        const int* P = pos + (int64_t)(2 * l + mu) * list_stride(dm.max_tokens);
+        const float* y = u + (int64_t)gload<int>(P + my) * Ld.kv_rs;
+        rmax = -INFINITY;
+        for (int t = t0; t < t1; ++t) {
+          __syncthreads();  // every wave is done with the norms
+          if (threadIdx.x < kScoreTile) jinv[0][threadIdx.x] = jinv_of(t);
+          __syncthreads();
+#pragma unroll 1
+          for (int rb = 0; rb < 2; ++rb) {
+            const int at = min(t * kScoreTile + rb * 32 + (lane & 31), K - 1);
+            floatx16 acc = mma_f32<D>(u + (int64_t)gload<int>(P + at) * Ld.kv_rs, y, half);
+            merge(acc, t * kScoreTile + rb * 32, &jinv[0][rb * 32]);
+          }
+        }
       }
       // both lane halves hold different tile rows of the same register row
       const float m = fmaxf(rmax, __shfl_xor(rmax, 32, 64));
@@ -1255,19 +1272,24 @@ void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, c
     return;
   }
   const dim3 glist((unsigned)((dm.max_tokens + kListRows - 1) / kListRows), dm.Hkv, dm.L);
-  uint16_t* perm = ws.perm;
   if constexpr (sizeof(T) == 2) {  // bf16: each pair once, rows gathered through the row lists
     OMNIMEM_LAUNCH(ws, K_NORMS, st,
                    lists_norms<T, D, false><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts,
-                                                                   perm, ws.odd_kv, ws.inv_norm, ws.best));
+                                                                   nullptr, ws.odd_kv, ws.inv_norm, ws.best));
     OMNIMEM_LAUNCH(ws, K_GRAM_SYM, st,
                    gram_sym<D><<<ws.gram_grid, 256, 0, st>>>(desc, dm, on_keys, ws.counts, ws.pos, ws.inv_norm, ws.best));
     OMNIMEM_LAUNCH(ws, K_GRAM_FINISH, st, gram_finish<<<gtok, 256, 0, st>>>(desc, dm, ws.pos, ws.counts, ws.best, s));
     return;
   }
-  OMNIMEM_LAUNCH(ws, K_NORMS, st,
-                 lists_norms<T, D, true><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, perm,
-                                                                ws.odd_kv, ws.inv_norm, ws.best));
+  uint16_t* perm = ws.split_kv;
+  if (perm)
+    OMNIMEM_LAUNCH(ws, K_NORMS, st,
+                   lists_norms<T, D, true><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, perm, ws.odd_kv,
+                                                                  ws.inv_norm, ws.best));
+  else
+    OMNIMEM_LAUNCH(ws, K_NORMS, st,
+                   lists_norms<T, D, false><<<glist, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, perm, ws.odd_kv,
+                                                                   ws.inv_norm, ws.best));
   const bool by_xcd = dm.L * dm.Hkv >= 2 * kXcds && ws.gram_grid % kXcds == 0;
   if (by_xcd)
     OMNIMEM_LAUNCH(ws, K_GRAM, st,

@@ -84,7 +84,7 @@ __device__ inline void online_update(const floatx16& acc, float sl2, float& m, f
 }
 
 
-// fp32 rows as three-part bf16 rows (SplitTile), written by split_rows.
+// fp32 rows as three-part bf16 rows (SplitTile), written by split_rows (null: there are none, see Workspace).
 struct SplitRows {
   const uint16_t* q;  // [L][Hq][max_chunk][3 D]
   const uint16_t* k;  // [L][Hkv][max_tokens][3 D]
@@ -327,7 +327,8 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int, int
 // (234 us with the 32x32x2 fp32 MFMA), the column sums 86 us (174 us); one
 // layer x 28 heads, 1500 queries, 4500 keys of width 128: 243 us (516 us, with
 // 123 registers spilled) and 242 us (504 us).  A segment with a value that the parts do not serve
-// is multiplied as fp32, from the rows themselves.
+// is done again as fp32, from the rows themselves (the flags are asked for at its start and
+// looked at when its tiles are done, so that no ordinary segment waits for them).
 template <int D>
 __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int l, int h, int q0, int kr0, int kr1,
                                        int64_t pslot, uint16_t* kt0, uint16_t* kt1, const SplitRows& sr,
@@ -342,14 +343,16 @@ __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int 
   const bool active = qw < C;
   const int kend_wave = min(kr1, dm.causal ? min(N, nc + min(qw + 32, C)) : N);
   auto copy = [&](uint16_t* lds, int t) { Tl::template copy<W>(lds, k + (int64_t)t * Tl::ROW, min(kTile, N - t)); };
-  copy(kt0, kr0);
   bf16x8 qf[Tl::NKS][3];
-  Tl::gload_all(qf, q + (int64_t)min(qw + (lane & 31), C - 1) * Tl::ROW, half);
-  // (the workgroup's rows and keys: every wave finds the same)
-  const bool odd = any_odd(sr.odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk), q0 / kSplitRows,
-                           (min(q0 + kBlockRows, C) + kSplitRows - 1) / kSplitRows) ||
-                   any_odd(sr.odd_k + ((int64_t)l * dm.Hkv + h / dm.G) * odd_stride(dm.max_tokens), kr0 / kSplitRows,
-                           (kr1 + kSplitRows - 1) / kSplitRows);
+  int flags = 1;  // of the workgroup's queries and keys: every wave finds the same
+  if (sr.q) {
+    copy(kt0, kr0);
+    flags = odd_flags(sr.odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk), q0 / kSplitRows,
+                      (min(q0 + kBlockRows, C) + kSplitRows - 1) / kSplitRows) |
+            odd_flags(sr.odd_k + ((int64_t)l * dm.Hkv + h / dm.G) * odd_stride(dm.max_tokens), kr0 / kSplitRows,
+                      (kr1 + kSplitRows - 1) / kSplitRows);
+    Tl::gload_all(qf, q + (int64_t)min(qw + (lane & 31), C - 1) * Tl::ROW, half);
+  }
   const float sl2 = Ld.scale_log2;
   float m = -1e30f, lsum = 0.0f;
   auto mask = [&](floatx16& acc, int kb) {
@@ -373,20 +376,20 @@ __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int 
     online_update(a0, sl2, m, lsum);
     online_update(a1, sl2, m, lsum);
   };
-  if (odd) {
+  for (int t = kr0; sr.q && t < kr1; t += 2 * kTile) {
+    step(t, kt0, kt1);
+    if (t + kTile < kr1) step(t + kTile, kt1, kt0);
+  }
+  if (__any(flags)) {
     const float* q32 = reinterpret_cast<const float*>(Ld.q) + (int64_t)h * Ld.q_hs;
     const float* k32 = reinterpret_cast<const float*>(Ld.k) + (int64_t)(h / dm.G) * Ld.kv_hs;
+    m = -1e30f;
+    lsum = 0.0f;
     for (int t = kr0; active && t < kend_wave; t += 32) {
       floatx16 acc = mma_f32<D>(k32 + (int64_t)min(t + (lane & 31), N - 1) * Ld.kv_rs,
                                 q32 + (int64_t)min(qw + (lane & 31), C - 1) * Ld.q_rs, half);
       mask(acc, t);
       online_update(acc, sl2, m, lsum);
-    }
-    dma_wait();
-  } else {
-    for (int t = kr0; t < kr1; t += 2 * kTile) {
-      step(t, kt0, kt1);
-      if (t + kTile < kr1) step(t + kTile, kt1, kt0);
     }
   }
   if (!active) return;
@@ -751,15 +754,18 @@ __device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, i
   auto copy = [&](uint16_t* lds, int t) { Tl::template copy<W>(lds, q + (int64_t)t * Tl::ROW, min(kTile, C - t)); };
   float lse_next = 0.0f;
   if (qstart < C) {
-    copy(qt0, qstart);
+    if (sr.q) copy(qt0, qstart);
     lse_next = load_lse(qstart);
   }
   bf16x8 kf[Tl::NKS][3];
-  Tl::gload_all(kf, k + (int64_t)min(kw + (lane & 31), N - 1) * Tl::ROW, half);
-  const bool odd = any_odd(sr.odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk), qstart / kSplitRows,
-                           (C + kSplitRows - 1) / kSplitRows) ||
-                   any_odd(sr.odd_k + ((int64_t)l * dm.Hkv + h / dm.G) * odd_stride(dm.max_tokens), k0 / kSplitRows,
-                           (min(k0 + kBlockRows, N) + kSplitRows - 1) / kSplitRows);
+  int flags = 1;
+  if (sr.q) {
+    flags = odd_flags(sr.odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk), qstart / kSplitRows,
+                      (C + kSplitRows - 1) / kSplitRows) |
+            odd_flags(sr.odd_k + ((int64_t)l * dm.Hkv + h / dm.G) * odd_stride(dm.max_tokens), k0 / kSplitRows,
+                      (min(k0 + kBlockRows, N) + kSplitRows - 1) / kSplitRows);
+    Tl::gload_all(kf, k + (int64_t)min(kw + (lane & 31), N - 1) * Tl::ROW, half);
+  }
   const float sl2 = Ld.scale_log2;
   float cs[1] = {0.0f};
   auto mask = [&](floatx16& acc, int qb) {
@@ -787,13 +793,18 @@ __device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, i
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) colsum_update(acc[rb], &lse2[i][rb * 32], half, sl2, cs);
   };
-  if (odd) {
+  for (int qt = qstart; sr.q && qt < C; qt += 2 * kTile) {
+    step(qt, 0, qt0, qt1);
+    if (qt + kTile < C) step(qt + kTile, 1, qt1, qt0);
+  }
+  if (__any(flags)) {  // (every wave of the workgroup, or none)
     const float* q32 = reinterpret_cast<const float*>(Ld.q) + (int64_t)h * Ld.q_hs;
     const float* k32 = reinterpret_cast<const float*>(Ld.k) + (int64_t)(h / dm.G) * Ld.kv_hs;
-    for (int qt = qstart, i = 0; qt < C; qt += kTile, i ^= 1) {
-      if (threadIdx.x < kTile) lse2[i][threadIdx.x] = lse_next;
+    cs[0] = 0.0f;
+    for (int qt = qstart; qt < C; qt += kTile) {
+      __syncthreads();  // every wave is done with the normalisers
+      if (threadIdx.x < kTile) lse2[0][threadIdx.x] = load_lse(qt);
       __syncthreads();
-      if (qt + kTile < C) lse_next = load_lse(qt + kTile);
       if (!active || qt + kTile <= qfirst_wave) continue;
 #pragma unroll 1
       for (int rb = 0; rb < 2; ++rb) {
@@ -801,14 +812,8 @@ __device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, i
         acc[0] = mma_f32<D>(q32 + (int64_t)min(qt + rb * 32 + (lane & 31), C - 1) * Ld.q_rs,
                             k32 + (int64_t)min(kw + (lane & 31), N - 1) * Ld.kv_rs, half);
         mask(acc[0], qt + rb * 32);
-        colsum_update(acc, &lse2[i][rb * 32], half, sl2, cs);
+        colsum_update(acc, &lse2[0][rb * 32], half, sl2, cs);
       }
-    }
-    dma_wait();
-  } else {
-    for (int qt = qstart; qt < C; qt += 2 * kTile) {
-      step(qt, 0, qt0, qt1);
-      if (qt + kTile < C) step(qt + kTile, 1, qt1, qt0);
     }
   }
   if (!active) return;
@@ -956,13 +961,16 @@ __global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ 
     const int r = (int)blockIdx.x * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
     if (r < rows) v[p] = gload16(src + (int64_t)r * rs + e);
   }
-  bool served = true;
+  SplitRange range;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const int r = (int)blockIdx.x * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
-    if (r < rows) served &= store_split(dst + (int64_t)r * 3 * D + e, D, v[p]);
+    if (r < rows) {
+      store_split(dst + (int64_t)r * 3 * D + e, D, v[p]);
+      range.add(v[p]);
+    }
   }
-  const int odd = __syncthreads_or(!served);
+  const int odd = __syncthreads_or(!range.serves());
   if (threadIdx.x == 0)
     (is_q ? odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk)
           : odd_k + ((int64_t)l * dm.Hkv + h) * odd_stride(dm.max_tokens))[blockIdx.x] = odd ? 1 : 0;
@@ -972,10 +980,12 @@ template <typename T, int D>
 void launch_typed(const Dims& dm, const LayerDesc* desc, const Workspace& ws, const PassPlan& lp,
                   const PassPlan& cp, float* lse_out, float* a, hipStream_t st) {
   constexpr int kTh = PassShape<T, D>::THREADS;
-  const SplitRows sr{ws.split_q, ws.split_k, ws.odd_q, ws.odd_kv};
+  const SplitRows sr{ws.split_q, ws.split_kv, ws.odd_q, ws.odd_kv};
   if constexpr (sizeof(T) == 4) {
     const dim3 gs((unsigned)((std::max(dm.max_tokens, dm.max_chunk) + kSplitRows - 1) / kSplitRows), dm.Hq + dm.Hkv, dm.L);
-    OMNIMEM_LAUNCH(ws, K_SPLIT, st, split_rows<D><<<gs, 256, 0, st>>>(desc, dm, ws.split_q, ws.split_k, ws.odd_q, ws.odd_kv));
+    if (sr.q)
+      OMNIMEM_LAUNCH(ws, K_SPLIT, st,
+                     split_rows<D><<<gs, 256, 0, st>>>(desc, dm, ws.split_q, ws.split_kv, ws.odd_q, ws.odd_kv));
   }
   if (lp.W > 0)
     OMNIMEM_LAUNCH(ws, K_LSE, st, lse_pass<T, D><<<lp.P, kTh, 0, st>>>(desc, dm, lp, sr, ws.lse_part));
