@@ -97,6 +97,7 @@ struct PassPlan {
   int P;      // workgroups
   int c;      // tiles per chunk
   int segs;   // partials per row
+  int longest;  // rows of the call's longest layer: its chunk (LSE pass), its working set (column sums)
 };
 // First partial of block b of head h in a layer whose rows start at `rbase`, n rows in blocks.
 __host__ __device__ inline int64_t plan_slot(const PassPlan& p, int64_t rbase, int h, int n, int b) {

@@ -937,18 +937,22 @@ __global__ void head_sum(const LayerDesc* __restrict__ layers, Dims dm, PassPlan
 }
 
 // fp32 queries and keys of every layer as three-part rows: four elements per
-// thread, the query heads' rows, then the KV heads'; and the workgroup's flag.
+// thread; and the workgroup's flag.  Grid: (H_q x q_blocks, the query heads'
+// workgroups, then H_kv x k_blocks; L): as many as the call's longest chunk and working set have
+// blocks, not the context's capacity (4 layers x (28 + 4) heads, 500 + 200 rows in
+// a context of 40960 rows: a score call 167 -> 128 us).
 template <int D>
-__global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ layers, Dims dm, uint16_t* __restrict__ sq,
-                                                  uint16_t* __restrict__ sk, uint8_t* __restrict__ odd_q,
-                                                  uint8_t* __restrict__ odd_k) {
+__global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ layers, Dims dm, int q_blocks,
+                                                  int k_blocks, uint16_t* __restrict__ sq, uint16_t* __restrict__ sk,
+                                                  uint8_t* __restrict__ odd_q, uint8_t* __restrict__ odd_k) {
   constexpr int TPR = D / 4, RPB = 256 / TPR;  // threads per row, rows per workgroup and step
-  const int l = blockIdx.z, head = blockIdx.y;
+  const int l = blockIdx.y;
   const LayerDesc& Ld = layers[l];
-  const bool is_q = head < dm.Hq;
-  const int h = is_q ? head : head - dm.Hq;
+  const bool is_q = (int)blockIdx.x < dm.Hq * q_blocks;
+  const int x = is_q ? (int)blockIdx.x : (int)blockIdx.x - dm.Hq * q_blocks;
+  const int h = x / (is_q ? q_blocks : k_blocks), block = x % (is_q ? q_blocks : k_blocks);
   const int rows = is_q ? Ld.n_chunk : Ld.n;
-  if ((int)blockIdx.x * kSplitRows >= rows) return;  // the whole workgroup
+  if (block * kSplitRows >= rows) return;  // the whole workgroup
   const float* src = reinterpret_cast<const float*>(is_q ? Ld.q : Ld.k) + (int64_t)h * (is_q ? Ld.q_hs : Ld.kv_hs);
   const int64_t rs = is_q ? Ld.q_rs : Ld.kv_rs;
   uint16_t* dst = is_q ? sq + ((int64_t)l * dm.Hq + h) * dm.max_chunk * 3 * D
@@ -958,13 +962,13 @@ __global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ 
   uint4 v[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    const int r = (int)blockIdx.x * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
+    const int r = block * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
     if (r < rows) v[p] = gload16(src + (int64_t)r * rs + e);
   }
   SplitRange range;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    const int r = (int)blockIdx.x * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
+    const int r = block * kSplitRows + p * RPB + (int)threadIdx.x / TPR;
     if (r < rows) {
       store_split(dst + (int64_t)r * 3 * D + e, D, v[p]);
       range.add(v[p]);
@@ -973,7 +977,7 @@ __global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ 
   const int odd = __syncthreads_or(!range.serves());
   if (threadIdx.x == 0)
     (is_q ? odd_q + ((int64_t)l * dm.Hq + h) * odd_stride(dm.max_chunk)
-          : odd_k + ((int64_t)l * dm.Hkv + h) * odd_stride(dm.max_tokens))[blockIdx.x] = odd ? 1 : 0;
+          : odd_k + ((int64_t)l * dm.Hkv + h) * odd_stride(dm.max_tokens))[block] = odd ? 1 : 0;
 }
 
 template <typename T, int D>
@@ -982,10 +986,11 @@ void launch_typed(const Dims& dm, const LayerDesc* desc, const Workspace& ws, co
   constexpr int kTh = PassShape<T, D>::THREADS;
   const SplitRows sr{ws.split_q, ws.split_kv, ws.odd_q, ws.odd_kv};
   if constexpr (sizeof(T) == 4) {
-    const dim3 gs((unsigned)((std::max(dm.max_tokens, dm.max_chunk) + kSplitRows - 1) / kSplitRows), dm.Hq + dm.Hkv, dm.L);
+    const int qb = (lp.longest + kSplitRows - 1) / kSplitRows, kb = (cp.longest + kSplitRows - 1) / kSplitRows;
     if (sr.q)
       OMNIMEM_LAUNCH(ws, K_SPLIT, st,
-                     split_rows<D><<<gs, 256, 0, st>>>(desc, dm, ws.split_q, ws.split_kv, ws.odd_q, ws.odd_kv));
+                     split_rows<D><<<dim3(dm.Hq * qb + dm.Hkv * kb, dm.L), 256, 0, st>>>(desc, dm, qb, kb, ws.split_q, ws.split_kv,
+                                                                                  ws.odd_q, ws.odd_kv));
   }
   if (lp.W > 0)
     OMNIMEM_LAUNCH(ws, K_LSE, st, lse_pass<T, D><<<lp.P, kTh, 0, st>>>(desc, dm, lp, sr, ws.lse_part));
@@ -1008,7 +1013,7 @@ void launch_typed(const Dims& dm, const LayerDesc* desc, const Workspace& ws, co
 // left slots idle (8 heads, 400 + 200 rows: 21.4, 27.9 and 37.1 us with one, two
 // and four) and no faster elsewhere.
 PassPlan choose_plan(int64_t W, int64_t rows, int t_max, int segs, int max_workgroups) {
-  PassPlan p{W, 0, 1, segs};
+  PassPlan p{W, 0, 1, segs, 0};
   if (W <= 0) return p;
   if (rows >= 8 * (int64_t)max_workgroups && rows < (int64_t{1} << 31) / 2) {
     p.W = rows;
@@ -1036,9 +1041,11 @@ PassPlan choose_plan(int64_t W, int64_t rows, int t_max, int segs, int max_workg
 // Fill each layer's tile bases of both score passes and the two plans.
 void plan_score(const Dims& dm, LayerDesc* layers, int max_workgroups, PassPlan* lse_plan, PassPlan* cs_plan) {
   int64_t lse_w = 0, cs_w = 0, lse_rows = 0, cs_rows = 0;
-  int lse_tmax = 0, cs_tmax = 0;
+  int lse_tmax = 0, cs_tmax = 0, chunk = 0, rows = 0;
   for (int l = 0; l < dm.L; ++l) {
     LayerDesc& x = layers[l];
+    chunk = std::max(chunk, x.n_chunk);
+    rows = std::max(rows, x.n);
     int th = 0, nb = 0;
     if (!x.lse_in) {
       for (int b = 0; b * kBlockRows < x.n_chunk; ++b, ++nb) {
@@ -1067,6 +1074,8 @@ void plan_score(const Dims& dm, LayerDesc* layers, int max_workgroups, PassPlan*
   }
   *lse_plan = choose_plan(lse_w, lse_rows, lse_tmax, plan_segs((int64_t)dm.L * dm.Hq * dm.qb, lse_rows), max_workgroups);
   *cs_plan = choose_plan(cs_w, cs_rows, cs_tmax, plan_segs((int64_t)dm.L * dm.Hq * dm.kb, cs_rows), max_workgroups);
+  lse_plan->longest = chunk;
+  cs_plan->longest = rows;
 }
 
 hipError_t launch_score(const Dims& dm, int dtype, const LayerDesc* desc, const Workspace& ws,
