@@ -394,8 +394,8 @@ def run_static(args, torch):
 
     graph, launch = None, "stream"
     if args.graph:
-        # The step's layer table is uploaded by the warmup: the captured calls
-        # launch kernels only.  A capture that fails leaves the stream mode.
+        # The captured calls launch kernels only: the step's, and the store of
+        # its layer table.  A capture that fails leaves the stream mode.
         try:
             graph_stream = torch.cuda.Stream()
             graph_stream.wait_stream(stream)

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -58,7 +59,16 @@ void prof_mark(Profiler* p, int kid, hipStream_t st, bool begin) {
 static const char* kKernelNames[K_COUNT] = {
     "lse_pass", "lse_merge", "colsum_pass", "head_sum", "modality_lists", "lists_norms", "gram_pass", "gram_finish", "adjacent_cos", "avba_partials", "avba_allocate", "psi_topk", "gather_compact",
     "gather_hidden", "adjacent_cos_hidden", "hidden_norms", "gram_wide", "hidden_finish", "layer_inputs",
-    "stage_moved_back", "gather_inplace", "append_chunk", "gram_sym", "topk_hist", "topk_bin", "topk_emit", "psi_topk_reg", "split_rows"};
+    "stage_moved_back", "gather_inplace", "append_chunk", "gram_sym", "topk_hist", "topk_bin", "topk_emit", "psi_topk_reg", "split_rows", "layer_table"};
+
+// A layer table on the device (see upload): where it is and what was copied there.
+struct DeviceTable {
+  int slot = -1, next = 0;
+  std::vector<LayerDesc> table;
+  bool has_chunks = false;              // an append's: its chunk fields are filled in
+  hipStream_t stream = nullptr;         // the stream of the copy
+  unsigned long long capture = 0;       // and its capture
+};
 
 struct omnimem_ctx {
   omnimem_config cfg;
@@ -67,14 +77,11 @@ struct omnimem_ctx {
   Workspace ws{};
   LayerDesc* pinned = nullptr;          // host ring [kSlots][L]
   const LayerDesc* pinned_dev = nullptr;  // its device address
-  hipEvent_t ev[kSlots] = {};
+  hipEvent_t ev[kSlots] = {};           // the slot's calls are done
   bool ev_used[kSlots] = {};
-  int next_slot = 0;
-  int last_slot = -1;                   // slot holding the last uploaded table
-  std::vector<LayerDesc> last_table;    // its chunk fields cleared
-  bool last_has_chunks = false;         // an append's table, chunk fields filled in
-  bool last_captured = false;           // its copy was recorded into a graph, not run
-  hipStream_t last_stream = nullptr;    // the stream of its copy
+  DeviceTable eager;                    // the last table copied by a call that ran
+  DeviceTable captured;                 // the last one whose copy was recorded into a graph
+  bool in_capture = false;              // the last call's
   PassPlan lse_plan{}, cs_plan{};  // score-pass plans of the last table
   int max_workgroups = 512;               // persistent score-pass grid: 2 per compute unit
   int calib_steps = 0;                    // steps in the calibration sums since the last reset
@@ -273,8 +280,8 @@ omnimem_status validate_append(omnimem_ctx* ctx, const omnimem_layer* layers, co
 }
 
 // Device descriptor of one layer (the score-pass plan fields are filled by
-// plan_score, an append's chunk fields by upload).
-void describe(const omnimem_config& cfg, const omnimem_layer& s, LayerDesc* out) {
+// plan_score).
+void describe(const omnimem_config& cfg, const omnimem_layer& s, const omnimem_chunk* chunk, LayerDesc* out) {
   LayerDesc& x = *out;
   std::memset(&x, 0, sizeof x);
   x.q = s.q; x.k = s.k; x.v = s.v; x.mod = s.modality; x.lse_in = s.lse;
@@ -290,10 +297,16 @@ void describe(const omnimem_config& cfg, const omnimem_layer& s, LayerDesc* out)
   x.mod_out = s.modality_out;
   x.out_cap = (int32_t)std::min<int64_t>(s.out_rows > 0 ? s.out_rows : x.n, x.n);
   x.inplace = (s.k_out && in_place(s)) ? 1 : 0;
+  if (chunk) {
+    x.ck = chunk->k; x.cv = chunk->v; x.cmod = chunk->modality;
+    x.c_hs = chunk->head_stride; x.c_rs = chunk->row_stride;
+  }
   const double log2e = 1.4426950408889634;
   const double scale = s.sm_scale != 0.0f ? (double)s.sm_scale : 1.0 / std::sqrt((double)cfg.head_dim);
   x.scale_log2 = (float)(scale * log2e);
 }
+
+static_assert(sizeof(LayerDesc) % 8 == 0 && alignof(LayerDesc) == 8, "whole words");
 
 // One ring slot's descriptors from pinned host memory to the device.  Read past the caches: the
 // slot's lines may hold an earlier table.
@@ -301,71 +314,110 @@ __global__ __launch_bounds__(256) void copy_descs(uint64_t* __restrict__ dst, co
   const int i = (int)(blockIdx.x * 256 + threadIdx.x);
   if (i < words) dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-static_assert(sizeof(LayerDesc) % 8 == 0 && alignof(LayerDesc) == 8, "whole words");
 
-// Copy the descriptor table to the device unless it equals the last one.
-// Only append reads the chunk fields, so the calls that follow an append on
-// its stream take the append's table when all else is equal (not inside or
-// after a stream capture: that copy has not run yet).  The copy is a kernel, whose launch
-// costs the stream less than a copy command.  A stream of ten 256-row chunks through
+// Layer descriptors passed by value.
+constexpr int kDescPerStore = 8;
+struct DescBlock {
+  uint64_t w[kDescPerStore * (sizeof(LayerDesc) / 8)];
+};
+static_assert(sizeof(DescBlock) <= 3072, "kernel argument block too large");
+
+__global__ __launch_bounds__(256) void store_descs(uint64_t* __restrict__ dst, DescBlock blk, int words) {
+  for (int i = (int)threadIdx.x; i < words; i += 256) dst[i] = blk.w[i];
+}
+
+void store_table(LayerDesc* dst, const LayerDesc* table, int L, hipStream_t st) {
+  for (int l0 = 0; l0 < L; l0 += kDescPerStore) {
+    const int count = std::min(kDescPerStore, L - l0);
+    DescBlock blk;
+    std::memcpy(blk.w, table + l0, sizeof(LayerDesc) * count);
+    store_descs<<<1, 256, 0, st>>>(reinterpret_cast<uint64_t*>(dst + l0), blk, (int)(sizeof(LayerDesc) / 8 * count));
+  }
+}
+
+// Whether `t` is what the device table holds, as far as a call without chunks
+// (an append, with them) reads it.
+bool holds(const DeviceTable& d, const std::vector<LayerDesc>& t, bool chunks) {
+  if (d.slot < 0 || d.table.size() != t.size() || (chunks && !d.has_chunks)) return false;
+  const size_t bytes = chunks ? sizeof(LayerDesc) : offsetof(LayerDesc, ck);
+  for (size_t l = 0; l < t.size(); ++l)
+    if (std::memcmp(&d.table[l], &t[l], bytes) != 0) return false;
+  return true;
+}
+
+// Copy the descriptor table to the device unless it is there.
+// A call that runs takes the last such call's table when they are equal
+// (only append reads the chunk fields; an append's own table serves calls on
+// its stream).  Calls of a context are ordered, so a slot may be written while the calls that
+// read its last table are still queued.
+// A captured call never takes a table that lies outside its graph, which
+// later calls overwrite, nor leaves one to calls that run, since a recorded copy has not:
+// it takes the last one recorded into the same capture on its stream, or records a copy
+// whose values are kernel arguments (in the graph, with no host memory to
+// outlive it) into a slot of the second half.
+// Outside a capture the copy is a kernel that reads pinned memory, whose launch costs the stream less than a copy command.  A stream of ten 256-row chunks through
 // 3 layers: 1246 -> 1175 us; one layer's step of 6144 rows, by the events without a system-scope fence (see
 // omnimem_create), 248 -> 238 us.
 omnimem_status upload(omnimem_ctx* ctx, const omnimem_layer* layers, hipStream_t st, const LayerDesc** dev,
                       const omnimem_chunk* chunks = nullptr) {
   const int L = ctx->cfg.n_layers;
   std::vector<LayerDesc> t(L);
-  for (int l = 0; l < L; ++l) describe(ctx->cfg, layers[l], &t[l]);
+  for (int l = 0; l < L; ++l) describe(ctx->cfg, layers[l], chunks ? &chunks[l] : nullptr, &t[l]);
   plan_score(ctx->dm, t.data(), ctx->max_workgroups, &ctx->lse_plan, &ctx->cs_plan);
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (chunks || ctx->last_has_chunks) {
-    if (hipStreamIsCapturing(st, &capture) != hipSuccess) {  // (the null stream beside a capture: not known)
-      (void)hipGetLastError();
-      capture = hipStreamCaptureStatusActive;
-    }
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(st, &status, &id) != hipSuccess) {  // (the null stream beside a capture: not known)
+    (void)hipGetLastError();
+    status = hipStreamCaptureStatusActive;
+    id = 0;
   }
-  const bool captured = capture != hipStreamCaptureStatusNone;
-  const bool usable = !ctx->last_has_chunks || (!captured && !ctx->last_captured && st == ctx->last_stream);
-  if (!chunks && usable && ctx->last_slot >= 0 && ctx->last_table.size() == t.size() &&
-      std::memcmp(ctx->last_table.data(), t.data(), sizeof(LayerDesc) * L) == 0) {
-    *dev = ctx->ws.desc + (size_t)ctx->last_slot * L;
+  const bool captured = status != hipStreamCaptureStatusNone;
+  ctx->in_capture = captured;
+  DeviceTable& d = captured ? ctx->captured : ctx->eager;
+  const bool there = captured ? id != 0 && id == d.capture && st == d.stream : !d.has_chunks || st == d.stream;
+  LayerDesc* base = ctx->ws.desc + (size_t)(captured ? kSlots : 0) * L;
+  if (there && holds(d, t, chunks != nullptr)) {
+    *dev = base + (size_t)d.slot * L;
     return OMNIMEM_OK;
   }
-  const int slot = ctx->next_slot;
-  if (ctx->ev_used[slot]) {
-    hipError_t e = hipEventSynchronize(ctx->ev[slot]);
-    if (e != hipSuccess) return hip_fail(ctx, e, "descriptor ring wait");
-  }
-  LayerDesc* host = ctx->pinned + (size_t)slot * L;
-  std::memcpy(host, t.data(), sizeof(LayerDesc) * L);
-  if (chunks)
-    for (int l = 0; l < L; ++l) {
-      host[l].ck = chunks[l].k; host[l].cv = chunks[l].v; host[l].cmod = chunks[l].modality;
-      host[l].c_hs = chunks[l].head_stride; host[l].c_rs = chunks[l].row_stride;
+  const int slot = d.next;
+  LayerDesc* dst = base + (size_t)slot * L;
+  d.slot = -1;  // (until the copy is queued)
+  if (captured) {
+    OMNIMEM_LAUNCH(ctx->ws, K_TABLE, st, store_table(dst, t.data(), L, st));
+  } else {
+    if (ctx->ev_used[slot]) {
+      hipError_t e = hipEventSynchronize(ctx->ev[slot]);
+      if (e != hipSuccess) return hip_fail(ctx, e, "descriptor ring wait");
     }
-  LayerDesc* d = ctx->ws.desc + (size_t)slot * L;
-  const int words = (int)(sizeof(LayerDesc) / 8 * L);
-  copy_descs<<<(words + 255) / 256, 256, 0, st>>>(reinterpret_cast<uint64_t*>(d),
-                                                  reinterpret_cast<const uint64_t*>(ctx->pinned_dev + (size_t)slot * L),
-                                                  words);
+    std::memcpy(ctx->pinned + (size_t)slot * L, t.data(), sizeof(LayerDesc) * L);
+    const int words = (int)(sizeof(LayerDesc) / 8 * L);
+    OMNIMEM_LAUNCH(ctx->ws, K_TABLE, st,
+                   copy_descs<<<(words + 255) / 256, 256, 0, st>>>(
+                       reinterpret_cast<uint64_t*>(dst),
+                       reinterpret_cast<const uint64_t*>(ctx->pinned_dev + (size_t)slot * L), words));
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e, "descriptor upload");
-  ctx->last_slot = slot;
-  ctx->last_table = t;
-  ctx->last_has_chunks = chunks != nullptr;
-  ctx->last_captured = captured;
-  ctx->last_stream = st;
-  ctx->next_slot = (slot + 1) % kSlots;
-  *dev = d;
+  d.slot = slot;
+  d.next = (slot + 1) % kSlots;
+  d.table = std::move(t);
+  d.has_chunks = chunks != nullptr;
+  d.stream = st;
+  d.capture = id;
+  *dev = dst;
   return OMNIMEM_OK;
 }
 
 // Mark the slot in use by this call's work.
 omnimem_status finish(omnimem_ctx* ctx, hipError_t launch_err, hipStream_t st, const char* what) {
   if (launch_err != hipSuccess) return hip_fail(ctx, launch_err, what);
-  const int slot = ctx->last_slot;
-  hipError_t e = hipEventRecord(ctx->ev[slot], st);
-  if (e != hipSuccess) return hip_fail(ctx, e, "event record");
-  ctx->ev_used[slot] = true;
+  const int slot = ctx->eager.slot;
+  if (!ctx->in_capture && slot >= 0) {
+    hipError_t e = hipEventRecord(ctx->ev[slot], st);
+    if (e != hipSuccess) return hip_fail(ctx, e, "event record");
+    ctx->ev_used[slot] = true;
+  }
   ctx->err.clear();
   return OMNIMEM_OK;
 }
@@ -471,20 +523,6 @@ omnimem_status scratch_address(int device, void** out) {
   return OMNIMEM_OK;
 }
 
-// Layer descriptors passed by value and stored into the scratch table.
-constexpr int kDescPerStore = 8;
-struct DescBlock {
-  LayerDesc d[kDescPerStore];
-};
-static_assert(sizeof(DescBlock) <= 3072, "kernel argument block too large");
-
-__global__ void store_descs(LayerDesc* __restrict__ dst, DescBlock blk, int count) {
-  if (threadIdx.x != 0) return;
-#pragma unroll
-  for (int i = 0; i < kDescPerStore; ++i)
-    if (i < count) dst[i] = blk.d[i];
-}
-
 template <typename T>
 hipError_t dalloc(omnimem_ctx* ctx, T** p, size_t count) {
   void* q = nullptr;
@@ -535,7 +573,7 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
   ws.gram_grid = ctx->max_workgroups;
   ws.stage_rows = c.inplace_stage_rows;
   const size_t elt = c.dtype == OMNIMEM_BF16 ? 2 : 4;
-  if ((e = dalloc(ctx, &ws.desc, (size_t)kSlots * L)) != hipSuccess ||
+  if ((e = dalloc(ctx, &ws.desc, (size_t)2 * kSlots * L)) != hipSuccess ||
       (e = dalloc(ctx, &ws.lse_part, (size_t)plan_partials((int64_t)(L * Hq) * dm.qb) * kScoreBlock)) != hipSuccess ||
       (e = dalloc(ctx, &ws.lse2, L * Hq * Cm)) != hipSuccess ||
       (e = dalloc(ctx, &ws.part, (size_t)plan_partials((int64_t)(L * Hq) * dm.kb) * kScoreBlock)) != hipSuccess ||
@@ -693,11 +731,10 @@ omnimem_status omnimem_allocate_noalloc(const omnimem_config* cfg, const omnimem
   Workspace ws{};
   ws.stat_part = reinterpret_cast<double*>(static_cast<char*>(base) + desc_bytes);
   for (int l0 = 0; l0 < cfg->n_layers; l0 += kDescPerStore) {
-    DescBlock blk;
-    std::memset(&blk, 0, sizeof blk);
+    LayerDesc t[kDescPerStore];
     const int count = std::min(kDescPerStore, cfg->n_layers - l0);
-    for (int i = 0; i < count; ++i) describe(*cfg, layers[l0 + i], &blk.d[i]);
-    store_descs<<<1, 64, 0, stream>>>(table + l0, blk, count);
+    for (int i = 0; i < count; ++i) describe(*cfg, layers[l0 + i], nullptr, &t[i]);
+    store_table(table + l0, t, count, stream);
   }
   e = launch_allocate(dm, table, ws, a, s, total_budget, cfg->ratio_r, cfg->temperature, cfg->b_min_frac,
                       cfg->b_max_frac, budgets, stats, stream);
@@ -829,8 +866,8 @@ omnimem_status omnimem_append(omnimem_ctx* ctx, const omnimem_layer* layers, con
   const LayerDesc* dev = nullptr;
   if ((st = upload(ctx, layers, stream, &dev, chunks)) != OMNIMEM_OK) return st;
   if (max_rows == 0) return finish(ctx, hipSuccess, stream, "omnimem_append");
-  return finish(ctx, launch_append(ctx->dm, ctx->cfg.dtype, dev, ctx->ws, max_rows, stream), stream,
-                "omnimem_append launch");
+  return finish(ctx, launch_append(ctx->dm, ctx->cfg.dtype, dev, ctx->ws, max_rows, stream),
+                stream, "omnimem_append launch");
 }
 
 omnimem_status omnimem_set_topk_path(omnimem_ctx* ctx, int32_t path) {

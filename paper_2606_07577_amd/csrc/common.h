@@ -226,7 +226,7 @@ __host__ __device__ inline int64_t topk_stride(int64_t max_tokens) {
 enum KernelId {
   K_LSE, K_LSE_MERGE, K_COLSUM, K_HEADSUM, K_LISTS, K_NORMS, K_GRAM, K_GRAM_FINISH, K_ADJ,
   K_AVBA_PART, K_AVBA_ALLOC, K_TOPK, K_GATHER, K_GATHER_H, K_ADJ_H, K_NORMS_H, K_GRAM_H, K_FINISH_H, K_LAYER_IN,
-  K_STAGE, K_GATHER_IP, K_APPEND, K_GRAM_SYM, K_TOPK_HIST, K_TOPK_BIN, K_TOPK_EMIT, K_TOPK_REG, K_SPLIT, K_COUNT
+  K_STAGE, K_GATHER_IP, K_APPEND, K_GRAM_SYM, K_TOPK_HIST, K_TOPK_BIN, K_TOPK_EMIT, K_TOPK_REG, K_SPLIT, K_TABLE, K_COUNT
 };
 struct Profiler;
 void prof_mark(Profiler* p, int kernel, hipStream_t st, bool begin);
@@ -243,7 +243,7 @@ void prof_mark(Profiler* p, int kernel, hipStream_t st, bool begin);
 // Workspace owned by a context (device pointers), sized at creation.
 // ---------------------------------------------------------------------------
 struct Workspace {
-  LayerDesc* desc;        // [slots][L]
+  LayerDesc* desc;        // [2 slots][L] layer tables, those of graph captures in the second half
   float2* lse_part;       // [partials][256] partial (reference, sum) in log2 units
   float* lse2;            // [L][Hq][max_chunk] merged normaliser, log2 units
   float* part;            // [partials][256] partial column sums per query head

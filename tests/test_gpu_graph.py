@@ -1,8 +1,8 @@
 """The whole compression step captured into a HIP graph and replayed.
 
-The library allocates nothing after create and, once a step's layer table
-has been uploaded, issues only kernel launches and an event record per
-call, so a step can be captured on a stream and replayed.  Every replay
+The library allocates nothing after create and issues only kernel launches
+inside a capture (the layer table travels as kernel arguments), so a step
+can be captured on a stream and replayed.  Every replay
 (with other device work and synchronisations in between) must give what
 the eager step gives, bit for bit.
 """
