@@ -76,12 +76,10 @@ struct omnimem_ctx {
   int device = 0;
   Workspace ws{};
   LayerDesc* pinned = nullptr;          // host ring [kSlots][L]
-  const LayerDesc* pinned_dev = nullptr;  // its device address
-  hipEvent_t ev[kSlots] = {};           // the slot's calls are done
+  hipEvent_t ev[kSlots] = {};           // the slot's pinned table has been copied
   bool ev_used[kSlots] = {};
   DeviceTable eager;                    // the last table copied by a call that ran
   DeviceTable captured;                 // the last one whose copy was recorded into a graph
-  bool in_capture = false;              // the last call's
   PassPlan lse_plan{}, cs_plan{};  // score-pass plans of the last table
   int max_workgroups = 512;               // persistent score-pass grid: 2 per compute unit
   int calib_steps = 0;                    // steps in the calibration sums since the last reset
@@ -308,13 +306,6 @@ void describe(const omnimem_config& cfg, const omnimem_layer& s, const omnimem_c
 
 static_assert(sizeof(LayerDesc) % 8 == 0 && alignof(LayerDesc) == 8, "whole words");
 
-// One ring slot's descriptors from pinned host memory to the device.  Read past the caches: the
-// slot's lines may hold an earlier table.
-__global__ __launch_bounds__(256) void copy_descs(uint64_t* __restrict__ dst, const uint64_t* src, int words) {
-  const int i = (int)(blockIdx.x * 256 + threadIdx.x);
-  if (i < words) dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Layer descriptors passed by value.
 constexpr int kDescPerStore = 8;
 struct DescBlock {
@@ -355,9 +346,15 @@ bool holds(const DeviceTable& d, const std::vector<LayerDesc>& t, bool chunks) {
 // it takes the last one recorded into the same capture on its stream, or records a copy
 // whose values are kernel arguments (in the graph, with no host memory to
 // outlive it) into a slot of the second half.
-// Outside a capture the copy is a kernel that reads pinned memory, whose launch costs the stream less than a copy command.  A stream of ten 256-row chunks through
-// 3 layers: 1246 -> 1175 us; one layer's step of 6144 rows, by the events without a system-scope fence (see
-// omnimem_create), 248 -> 238 us.
+// Outside a capture up to kDescPerStore layers travel as arguments, too; more
+// by a copy command from pinned memory, one for any number.  An event marks
+// the end of that copy and nothing else: one behind every call, without a
+// system-scope fence, cost 2 us of the stream a call and 3 us of a wait for
+// it (which then needs a fence of its own).  A new table every call, in a row
+// and alone, in us: score of 5 layers, arguments 102 and 128, copy command
+// 103 and 129 (with an event behind every call 106 and 129); select of one
+// layer 14.7 and 30.7, 16.6 and 32.3 (19.8 and 31.4); redundancy of 28 layers, copy
+// command 17.4 and 31.0, a kernel that reads the pinned table 18.1 and 31.6.
 omnimem_status upload(omnimem_ctx* ctx, const omnimem_layer* layers, hipStream_t st, const LayerDesc** dev,
                       const omnimem_chunk* chunks = nullptr) {
   const int L = ctx->cfg.n_layers;
@@ -372,7 +369,6 @@ omnimem_status upload(omnimem_ctx* ctx, const omnimem_layer* layers, hipStream_t
     id = 0;
   }
   const bool captured = status != hipStreamCaptureStatusNone;
-  ctx->in_capture = captured;
   DeviceTable& d = captured ? ctx->captured : ctx->eager;
   const bool there = captured ? id != 0 && id == d.capture && st == d.stream : !d.has_chunks || st == d.stream;
   LayerDesc* base = ctx->ws.desc + (size_t)(captured ? kSlots : 0) * L;
@@ -383,7 +379,7 @@ omnimem_status upload(omnimem_ctx* ctx, const omnimem_layer* layers, hipStream_t
   const int slot = d.next;
   LayerDesc* dst = base + (size_t)slot * L;
   d.slot = -1;  // (until the copy is queued)
-  if (captured) {
+  if (captured || L <= kDescPerStore) {
     OMNIMEM_LAUNCH(ctx->ws, K_TABLE, st, store_table(dst, t.data(), L, st));
   } else {
     if (ctx->ev_used[slot]) {
@@ -391,11 +387,12 @@ omnimem_status upload(omnimem_ctx* ctx, const omnimem_layer* layers, hipStream_t
       if (e != hipSuccess) return hip_fail(ctx, e, "descriptor ring wait");
     }
     std::memcpy(ctx->pinned + (size_t)slot * L, t.data(), sizeof(LayerDesc) * L);
-    const int words = (int)(sizeof(LayerDesc) / 8 * L);
-    OMNIMEM_LAUNCH(ctx->ws, K_TABLE, st,
-                   copy_descs<<<(words + 255) / 256, 256, 0, st>>>(
-                       reinterpret_cast<uint64_t*>(dst),
-                       reinterpret_cast<const uint64_t*>(ctx->pinned_dev + (size_t)slot * L), words));
+    hipError_t e = hipSuccess;
+    OMNIMEM_LAUNCH(ctx->ws, K_TABLE, st, e = hipMemcpyAsync(dst, ctx->pinned + (size_t)slot * L, sizeof(LayerDesc) * L,
+                                                            hipMemcpyHostToDevice, st));
+    if (e != hipSuccess) return hip_fail(ctx, e, "descriptor upload");
+    if ((e = hipEventRecord(ctx->ev[slot], st)) != hipSuccess) return hip_fail(ctx, e, "event record");
+    ctx->ev_used[slot] = true;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e, "descriptor upload");
@@ -409,15 +406,8 @@ omnimem_status upload(omnimem_ctx* ctx, const omnimem_layer* layers, hipStream_t
   return OMNIMEM_OK;
 }
 
-// Mark the slot in use by this call's work.
-omnimem_status finish(omnimem_ctx* ctx, hipError_t launch_err, hipStream_t st, const char* what) {
+omnimem_status finish(omnimem_ctx* ctx, hipError_t launch_err, const char* what) {
   if (launch_err != hipSuccess) return hip_fail(ctx, launch_err, what);
-  const int slot = ctx->eager.slot;
-  if (!ctx->in_capture && slot >= 0) {
-    hipError_t e = hipEventRecord(ctx->ev[slot], st);
-    if (e != hipSuccess) return hip_fail(ctx, e, "event record");
-    ctx->ev_used[slot] = true;
-  }
   ctx->err.clear();
   return OMNIMEM_OK;
 }
@@ -603,24 +593,18 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
     return fail(nullptr, OMNIMEM_ERR_HIP, "workspace allocation: %s", hipGetErrorString(e));
   }
   void* pinned = nullptr;
-  if ((e = hipHostMalloc(&pinned, sizeof(LayerDesc) * kSlots * L, hipHostMallocCoherent)) != hipSuccess) {
+  if ((e = hipHostMalloc(&pinned, sizeof(LayerDesc) * kSlots * L, hipHostMallocDefault)) != hipSuccess) {
     omnimem_destroy(ctx);
     return fail(nullptr, OMNIMEM_ERR_HIP, "pinned descriptor ring: %s", hipGetErrorString(e));
   }
   ctx->pinned = static_cast<LayerDesc*>(pinned);
-  void* pinned_dev = nullptr;
-  if ((e = hipHostGetDevicePointer(&pinned_dev, pinned, 0)) != hipSuccess) {
-    omnimem_destroy(ctx);
-    return fail(nullptr, OMNIMEM_ERR_HIP, "pinned descriptor ring address: %s", hipGetErrorString(e));
-  }
-  ctx->pinned_dev = static_cast<const LayerDesc*>(pinned_dev);
   if ((e = hipMemset(ws.ctl, 0, 4 * sizeof(int))) != hipSuccess ||
       (e = hipMemset(ws.tk_hist, 0, L * Hkv * 2 * (size_t)kTopkBins * sizeof(int))) != hipSuccess) {
     omnimem_destroy(ctx);
     return fail(nullptr, OMNIMEM_ERR_HIP, "control words: %s", hipGetErrorString(e));
   }
   for (int i = 0; i < kSlots; ++i) {
-    // (the host waits on these only to rewrite a slot whose reads are done: no system-scope fence)
+    // (the host waits on these only to rewrite pinned memory whose copy is done: no system-scope fence)
     if ((e = hipEventCreateWithFlags(&ctx->ev[i], hipEventDisableTiming | hipEventDisableSystemFence)) != hipSuccess) {
       omnimem_destroy(ctx);
       return fail(nullptr, OMNIMEM_ERR_HIP, "event: %s", hipGetErrorString(e));
@@ -671,7 +655,7 @@ omnimem_status omnimem_score(omnimem_ctx* ctx, const omnimem_layer* layers, floa
   if ((st = upload(ctx, layers, stream, &dev)) != OMNIMEM_OK) return st;
   return finish(ctx, launch_score(ctx->dm, ctx->cfg.dtype, dev, ctx->ws, ctx->lse_plan, ctx->cs_plan, lse_out, a,
                                   stream),
-                stream, "omnimem_score launch");
+                "omnimem_score launch");
 }
 
 omnimem_status omnimem_redundancy(omnimem_ctx* ctx, const omnimem_layer* layers, float* s, hipStream_t stream) {
@@ -686,7 +670,7 @@ omnimem_status omnimem_redundancy(omnimem_ctx* ctx, const omnimem_layer* layers,
   if ((st = upload(ctx, layers, stream, &dev)) != OMNIMEM_OK) return st;
   return finish(ctx, launch_redundancy(ctx->dm, ctx->cfg.dtype, ctx->cfg.sim, ctx->cfg.sim_source, dev, ctx->ws,
                                        s, stream),
-                stream, "omnimem_redundancy launch");
+                "omnimem_redundancy launch");
 }
 
 omnimem_status omnimem_allocate(omnimem_ctx* ctx, const omnimem_layer* layers, const float* a, const float* s,
@@ -699,7 +683,7 @@ omnimem_status omnimem_allocate(omnimem_ctx* ctx, const omnimem_layer* layers, c
   if ((st = upload(ctx, layers, stream, &dev)) != OMNIMEM_OK) return st;
   return finish(ctx, launch_allocate(ctx->dm, dev, ctx->ws, a, s, total_budget, c.ratio_r, c.temperature,
                                      c.b_min_frac, c.b_max_frac, budgets, stats, stream),
-                stream, "omnimem_allocate launch");
+                "omnimem_allocate launch");
 }
 
 omnimem_status omnimem_allocate_noalloc(const omnimem_config* cfg, const omnimem_layer* layers, const float* a,
@@ -754,7 +738,7 @@ omnimem_status omnimem_calibrate(omnimem_ctx* ctx, const omnimem_layer* layers, 
   if ((st = upload(ctx, layers, stream, &dev)) != OMNIMEM_OK) return st;
   st = finish(ctx, launch_calibrate(ctx->dm, dev, ctx->ws, a, s, ctx->cfg.ratio_r, ctx->calib_steps == 0, stats,
                                     stream),
-              stream, "omnimem_calibrate launch");
+              "omnimem_calibrate launch");
   if (st == OMNIMEM_OK) ++ctx->calib_steps;
   return st;
 }
@@ -781,7 +765,7 @@ omnimem_status omnimem_calibration_budgets(omnimem_ctx* ctx, int64_t total_budge
   if (st != OMNIMEM_OK) return st;
   return finish(ctx, launch_calibration_budgets(ctx->dm, ctx->ws, total_budget, c.temperature, c.b_min_frac,
                                                 c.b_max_frac, ctx->calib_steps, layer_budgets, stream),
-                stream, "omnimem_calibration_budgets launch");
+                "omnimem_calibration_budgets launch");
 }
 
 omnimem_status omnimem_allocate_fixed(omnimem_ctx* ctx, const omnimem_layer* layers, const float* a, const float* s,
@@ -796,7 +780,7 @@ omnimem_status omnimem_allocate_fixed(omnimem_ctx* ctx, const omnimem_layer* lay
   if ((st = upload(ctx, layers, stream, &dev)) != OMNIMEM_OK) return st;
   return finish(ctx, launch_allocate_fixed(ctx->dm, dev, ctx->ws, a, s, layer_budgets, ctx->cfg.ratio_r, budgets,
                                            stats, stream),
-                stream, "omnimem_allocate_fixed launch");
+                "omnimem_allocate_fixed launch");
 }
 
 omnimem_status omnimem_select_compact(omnimem_ctx* ctx, const omnimem_layer* layers, const float* a, const float* s,
@@ -829,7 +813,7 @@ omnimem_status omnimem_select_compact(omnimem_ctx* ctx, const omnimem_layer* lay
   return finish(ctx, launch_select_compact(ctx->dm, ctx->cfg.dtype, ctx->cfg.lambda, ctx->cfg.shared_selection ? 1 : 0,
                                            hidden, inplace, (int)max_n, path, dev, ctx->ws, a, s, budgets, idx,
                                            stream),
-                stream, "omnimem_select_compact launch");
+                "omnimem_select_compact launch");
 }
 
 omnimem_status omnimem_inplace_status(omnimem_ctx* ctx, int64_t* rows_needed) {
@@ -865,9 +849,9 @@ omnimem_status omnimem_append(omnimem_ctx* ctx, const omnimem_layer* layers, con
   if ((st = set_device(ctx)) != OMNIMEM_OK) return st;
   const LayerDesc* dev = nullptr;
   if ((st = upload(ctx, layers, stream, &dev, chunks)) != OMNIMEM_OK) return st;
-  if (max_rows == 0) return finish(ctx, hipSuccess, stream, "omnimem_append");
+  if (max_rows == 0) return finish(ctx, hipSuccess, "omnimem_append");
   return finish(ctx, launch_append(ctx->dm, ctx->cfg.dtype, dev, ctx->ws, max_rows, stream),
-                stream, "omnimem_append launch");
+                "omnimem_append launch");
 }
 
 omnimem_status omnimem_set_topk_path(omnimem_ctx* ctx, int32_t path) {
