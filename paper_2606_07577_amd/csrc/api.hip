@@ -668,8 +668,8 @@ omnimem_status omnimem_redundancy(omnimem_ctx* ctx, const omnimem_layer* layers,
   if ((st = set_device(ctx)) != OMNIMEM_OK) return st;
   const LayerDesc* dev = nullptr;
   if ((st = upload(ctx, layers, stream, &dev)) != OMNIMEM_OK) return st;
-  return finish(ctx, launch_redundancy(ctx->dm, ctx->cfg.dtype, ctx->cfg.sim, ctx->cfg.sim_source, dev, ctx->ws,
-                                       s, stream),
+  return finish(ctx, launch_redundancy(ctx->dm, ctx->cfg.dtype, ctx->cfg.sim, ctx->cfg.sim_source, dev,
+                                       ctx->cs_plan.longest, ctx->ws, s, stream),
                 "omnimem_redundancy launch");
 }
 

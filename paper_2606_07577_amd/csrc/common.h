@@ -288,8 +288,8 @@ hipError_t launch_score(const Dims& dm, int dtype, const LayerDesc* desc, const 
                         hipStream_t st);
 void plan_score(const Dims& dm, LayerDesc* layers, int max_workgroups, PassPlan* lse_plan, PassPlan* cs_plan);
 int allocate_part_chunks(const Dims& dm);
-hipError_t launch_redundancy(const Dims& dm, int dtype, int sim, int on_keys, const LayerDesc* desc,
-                             const Workspace& ws, float* s, hipStream_t st);
+hipError_t launch_redundancy(const Dims& dm, int dtype, int sim, int source, const LayerDesc* desc, int longest,
+                             const Workspace& ws, float* s, hipStream_t st);  // longest: largest N of the call
 hipError_t launch_lists(const Dims& dm, const LayerDesc* desc, const Workspace& ws, hipStream_t st);
 hipError_t launch_allocate(const Dims& dm, const LayerDesc* desc, const Workspace& ws,
                            const float* a, const float* s, int64_t total, float ratio_r,

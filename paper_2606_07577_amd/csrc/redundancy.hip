@@ -525,15 +525,15 @@ __device__ inline void piece_f64(const uint4& p, double (&out)[16 / sizeof(T)]) 
 // Bound by HBM (the rows once, plus the two rows at the ends of a group from
 // L2).  One thread per row reading its three rows element by element took
 // 218 us on 28 layers of 6144 bf16 rows x 4 heads of 128 (0.8 TB/s); this
-// takes
-// 44.5 us (4.0 TB/s); 4 rows a group 51, 12 rows 44.0, 14 rows (176 registers) 52.
+// takes 44.5 us (4.0 TB/s); 4 rows a group 51, 12 rows 44.0, 14 rows (176
+// registers) 52.  (Hidden states choose R by size, see launch_hidden_adjacent.)
 template <int LPR> constexpr int adj_rows() { return LPR < 16 ? 6 : 8; }
 
-template <typename T, int LPR, bool HIDDEN>
+template <typename T, int LPR, int R, bool HIDDEN>
 __global__ __launch_bounds__(256) void adjacent_cos(const LayerDesc* __restrict__ layers, Dims dm, int on_keys,
                                                     const int* __restrict__ pos, const int* __restrict__ counts,
                                                     float* __restrict__ s) {
-  constexpr int R = adj_rows<LPR>(), V = R + 2, EPP = 16 / (int)sizeof(T);
+  constexpr int V = R + 2, EPP = 16 / (int)sizeof(T);
   static_assert(V <= LPR, "a lane of the group for every row's sum");
   const int l = blockIdx.z, g = blockIdx.y;
   const LayerDesc& Ld = layers[l];
@@ -1261,14 +1261,37 @@ __global__ __launch_bounds__(256, 2) void gram_sym(const LayerDesc* __restrict__
   }
 }
 
+template <typename T, int R>
+void launch_hidden_rows(const Dims& dm, const LayerDesc* desc, const Workspace& ws, int longest, float* s,
+                        hipStream_t st) {
+  constexpr int kRows = 256 / 64 * R;
+  const dim3 grid((unsigned)((longest + kRows - 1) / kRows), 1, dm.L);
+  OMNIMEM_LAUNCH(ws, K_ADJ_H, st, adjacent_cos<T, 64, R, true><<<grid, 256, 0, st>>>(desc, dm, 0, ws.pos, ws.counts, s));
+}
+
+// Rows per wavefront: more are read from HBM less often, fewer give a short
+// call more wavefronts.  bf16 hidden states, the call in us with 1, 2, 4 and 8
+// rows: 1 x 33 x 65536 (layers x rows x width) 42, 50, 66, 171; 1 x 500 x
+// 16384 17, 19, 24, 37; 1 x 1000 x 3584 11.8, 11.1, 12.1, 16.2; 1 x 6144 x
+// 3584 19.8, 17.4, 17.3, 21.5; 28 x 6144 x 3584 326, 249, 220, 229; rows of
+// one step of the lanes, 28 x 6144 x 256 120, 85, 69, 62.  (A wavefront per row reading its
+// three rows, before: 46, 26, 14.0, 26, 364 and 125.)
+template <typename T>
+void launch_hidden_adjacent(const Dims& dm, const LayerDesc* desc, const Workspace& ws, int longest, float* s,
+                            hipStream_t st) {
+  if ((int64_t)dm.L * longest < 4096) launch_hidden_rows<T, 1>(dm, desc, ws, longest, s, st);
+  else if (dm.dh * (int)sizeof(T) > 64 * 16) launch_hidden_rows<T, 4>(dm, desc, ws, longest, s, st);
+  else launch_hidden_rows<T, 8>(dm, desc, ws, longest, s, st);
+}
+
 template <typename T, int D>
 void launch_typed(const Dims& dm, int sim, int on_keys, const LayerDesc* desc, const Workspace& ws, float* s,
                   hipStream_t st) {
   const dim3 gtok((unsigned)((dm.max_tokens + 255) / 256), dm.Hkv, dm.L);
   if (sim == 1) {
-    constexpr int LPR = GatherShape<T, D>::LPR, kRows = 256 / LPR * adj_rows<LPR>();
+    constexpr int LPR = GatherShape<T, D>::LPR, R = adj_rows<LPR>(), kRows = 256 / LPR * R;
     const dim3 grid((unsigned)((dm.max_tokens + kRows - 1) / kRows), dm.Hkv, dm.L);
-    OMNIMEM_LAUNCH(ws, K_ADJ, st, adjacent_cos<T, LPR, false><<<grid, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, s));
+    OMNIMEM_LAUNCH(ws, K_ADJ, st, adjacent_cos<T, LPR, R, false><<<grid, 256, 0, st>>>(desc, dm, on_keys, ws.pos, ws.counts, s));
     return;
   }
   const dim3 glist((unsigned)((dm.max_tokens + kListRows - 1) / kListRows), dm.Hkv, dm.L);
@@ -1309,7 +1332,7 @@ hipError_t launch_lists(const Dims& dm, const LayerDesc* desc, const Workspace& 
   return hipGetLastError();
 }
 
-hipError_t launch_redundancy(const Dims& dm, int dtype, int sim, int source, const LayerDesc* desc,
+hipError_t launch_redundancy(const Dims& dm, int dtype, int sim, int source, const LayerDesc* desc, int longest,
                              const Workspace& ws, float* s, hipStream_t st) {
   if (sim == 1) {  // the all-pairs mode computes the lists inside lists_norms
     hipError_t e = launch_lists(dm, desc, ws, st);
@@ -1335,12 +1358,8 @@ hipError_t launch_redundancy(const Dims& dm, int dtype, int sim, int source, con
     return hipGetLastError();
   }
   if (source == 2) {  // hidden states, adjacent
-    constexpr int kRows = 256 / 64 * adj_rows<64>();
-    const dim3 grid((unsigned)((dm.max_tokens + kRows - 1) / kRows), 1, dm.L);
-    if (dtype == 0)
-      OMNIMEM_LAUNCH(ws, K_ADJ_H, st, adjacent_cos<uint16_t, 64, true><<<grid, 256, 0, st>>>(desc, dm, 0, ws.pos, ws.counts, s));
-    else
-      OMNIMEM_LAUNCH(ws, K_ADJ_H, st, adjacent_cos<float, 64, true><<<grid, 256, 0, st>>>(desc, dm, 0, ws.pos, ws.counts, s));
+    if (dtype == 0) launch_hidden_adjacent<uint16_t>(dm, desc, ws, longest, s, st);
+    else launch_hidden_adjacent<float>(dm, desc, ws, longest, s, st);
     return hipGetLastError();
   }
   const int on_keys = source == 1 ? 1 : 0;
