@@ -2,7 +2,10 @@
 // libomnimem_probe.so, used only for measurement).  Each kernel keeps every
 // SIMD busy with independent work for `iters` iterations and writes one value
 // per lane only when `flag` is set (it never is), so nothing is optimised
-// away and nothing but registers (and, in one probe, LDS) is touched.
+// away and nothing but registers (and, in one probe, LDS) is touched.  The
+// operands are near N(0, 1), as the passes' are: the chip slows down with
+// the bits that change from one product to the next (MFMA alone 1.76
+// PFLOP/s, against 2.36 on seven small values; probe_mix_bar 1.22 and 1.61).
 //
 //   probe_mfma      four independent chains of v_mfma_f32_32x32x16_bf16
 //   probe_exp       sixteen independent chains of v_exp_f32
@@ -37,17 +40,25 @@ __device__ inline floatx16 mma(bf16x8 a, bf16x8 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// Eight values of mean 0 and variance 1 (sums of four bytes of a hash).
 __device__ inline bf16x8 frag_of(int seed) {
   bf16x8 f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) f[i] = (__bf16)(0.001f * (float)((seed + i) & 7));
+  for (int i = 0; i < 8; ++i) {
+    uint32_t h = (uint32_t)(seed * 8 + i) * 0x9E3779B9u;
+    h = (h ^ (h >> 16)) * 0x85EBCA6Bu;
+    h = (h ^ (h >> 13)) * 0xC2B2AE35u;
+    h ^= h >> 16;
+    const int sum = (int)(h & 255u) + (int)((h >> 8) & 255u) + (int)((h >> 16) & 255u) + (int)(h >> 24);
+    f[i] = (__bf16)((float)(sum - 510) * (1.0f / 147.8f));
+  }
   return f;
 }
 
 constexpr int NKS = 8;   // k-steps of one 32x32 tile at head_dim 128
 
 __global__ __launch_bounds__(256) void probe_mfma(int iters, float* out, int flag) {
-  const bf16x8 a = frag_of(threadIdx.x), b = frag_of(threadIdx.x + 3);
+  const bf16x8 a = frag_of(threadIdx.x), b = frag_of(1024 + threadIdx.x);
   floatx16 c0 = {}, c1 = {}, c2 = {}, c3 = {};
   for (int it = 0; it < iters; ++it) {
     c0 = mma(a, b, c0);
@@ -130,9 +141,9 @@ __global__ __launch_bounds__(256, 2) void probe_mix(int iters, float* out, int f
   bf16x8 f[NKS], qf[2][NKS];
 #pragma unroll
   for (int k = 0; k < NKS; ++k) {
-    f[k] = frag_of(threadIdx.x + k);
-    qf[0][k] = frag_of(threadIdx.x + 2 * k);
-    qf[1][k] = frag_of(threadIdx.x + 3 * k);
+    f[k] = frag_of(512 + k * 256 + threadIdx.x);
+    qf[0][k] = frag_of(4096 + k * 256 + threadIdx.x);
+    qf[1][k] = frag_of(8192 + k * 256 + threadIdx.x);
   }
   floatx16 acc0[2] = {}, acc1[2] = {};
   float lsum[2] = {0.0f, 0.0f};
@@ -199,8 +210,8 @@ __global__ __launch_bounds__(256, 2) void probe_gram(int iters, float* out, int 
   float iv[2][16], rmax[2][16];
 #pragma unroll
   for (int k = 0; k < NKS; ++k) {
-    a[0][k] = frag_of(threadIdx.x + 2 * k);
-    a[1][k] = frag_of(threadIdx.x + 3 * k);
+    a[0][k] = frag_of(4096 + k * 256 + threadIdx.x);
+    a[1][k] = frag_of(8192 + k * 256 + threadIdx.x);
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
