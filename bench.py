@@ -20,6 +20,17 @@ if ROOT not in sys.path:
 METRIC = "KV tokens compressed/sec per layer-step; % MFMA peak (score+Gram), % HBM (top-k+compact)"
 PEAK_HBM_GBS = 8000.0                                   # MI355X HBM3E
 PEAK_MFMA_TFLOPS = {"bf16": 2500.0, "f32": 157.3}       # dense MFMA
+# fp32 products of these kernels are six bf16 products of the values' parts
+SPLIT_F32_KERNELS = ("lse_pass", "colsum_pass", "gram_pass")
+
+
+def peak_tflops(kernel, dtype):
+    """Peak rate of the matrix instructions the kernel runs, in the products it is counted by."""
+    if dtype == "f32" and kernel in SPLIT_F32_KERNELS:
+        return PEAK_MFMA_TFLOPS["bf16"] / 6
+    return PEAK_MFMA_TFLOPS[dtype]
+
+
 
 # HBM bytes per launch from two rocprofv3 counter passes (FETCH_SIZE, then
 # WRITE_SIZE, KiB per dispatch), each divided by what that counter reads for a
@@ -610,29 +621,29 @@ def main():
             bound, units = work[name]
             if bound == "mfma":
                 ach = units / (avg_ms / 1e3) / 1e12
-                entry.update(bound="mfma", achieved=ach, unit="TFLOP/s", frac=ach / PEAK_MFMA_TFLOPS[dtype])
+                entry.update(bound="mfma", achieved=ach, unit="TFLOP/s", frac=ach / peak_tflops(name, dtype))
             else:
                 ach = units / (avg_ms / 1e3) / 1e9
                 entry.update(bound="hbm", achieved=ach, unit="GB/s", frac=ach / PEAK_HBM_GBS)
         per_kernel[name] = entry
     dominant = max((n for n in per_kernel if n in work), key=lambda n: per_kernel[n]["avg_us"])
     dk = per_kernel[dominant]
-    peak = PEAK_MFMA_TFLOPS[dtype] if dk["bound"] == "mfma" else PEAK_HBM_GBS
+    peak = peak_tflops(dominant, dtype) if dk["bound"] == "mfma" else PEAK_HBM_GBS
     roofline = {"bound": dk["bound"], "achieved": round(dk["achieved"], 3), "peak": peak, "unit": dk["unit"],
                 "frac": round(dk["frac"], 4), "traffic": measured_traffic(args.workload, dominant),
                 "traffic_unit": "bytes", "kernel": dominant,
                 "units_per_launch": work[dominant][1], "avg_launch_us": dk["avg_us"]}
 
     def stage_frac(names, peak_units, scale):
-        # time of every listed kernel that ran; units of those with algorithmic units (the
-        # in-place staging copy moves bytes beyond the out-of-place minimum: time only)
+        # time of every listed kernel that ran; units of those with algorithmic units, over the peak
+        # of each (the in-place staging copy moves bytes beyond the out-of-place minimum: time only)
         t = sum(per_kernel[n]["avg_us"] for n in names if n in per_kernel) / 1e6
-        u = sum(work[n][1] for n in names if n in per_kernel and n in work)
-        return round(u / t / scale / peak_units, 4) if t > 0 else None
+        u = sum(work[n][1] / peak_units(n) for n in names if n in per_kernel and n in work)
+        return round(u / t / scale, 4) if t > 0 else None
 
     fractions = {
-        "mfma_frac_score_gram": stage_frac(SCORE_GRAM_KERNELS, PEAK_MFMA_TFLOPS[dtype], 1e12),
-        "hbm_frac_topk_compact": stage_frac(TOPK_COMPACT_KERNELS, PEAK_HBM_GBS, 1e9),
+        "mfma_frac_score_gram": stage_frac(SCORE_GRAM_KERNELS, lambda n: peak_tflops(n, dtype), 1e12),
+        "hbm_frac_topk_compact": stage_frac(TOPK_COMPACT_KERNELS, lambda n: PEAK_HBM_GBS, 1e9),
     }
     out = {
         "metric": METRIC, "value": round(value, 1), "unit": "tokens/s", "n_gpus": 1, "steps": args.steps,
