@@ -336,25 +336,25 @@ bool holds(const DeviceTable& d, const std::vector<LayerDesc>& t, bool chunks) {
   return true;
 }
 
-// Copy the descriptor table to the device unless it is there.
-// A call that runs takes the last such call's table when they are equal
-// (only append reads the chunk fields; an append's own table serves calls on
-// its stream).  Calls of a context are ordered, so a slot may be written while the calls that
-// read its last table are still queued.
-// A captured call never takes a table that lies outside its graph, which
-// later calls overwrite, nor leaves one to calls that run, since a recorded copy has not:
-// it takes the last one recorded into the same capture on its stream, or records a copy
-// whose values are kernel arguments (in the graph, with no host memory to
-// outlive it) into a slot of the second half.
-// Outside a capture up to kDescPerStore layers travel as arguments, too; more
-// by a copy command from pinned memory, one for any number.  An event marks
-// the end of that copy and nothing else: one behind every call, without a
-// system-scope fence, cost 2 us of the stream a call and 3 us of a wait for
-// it (which then needs a fence of its own).  A new table every call, in a row
-// and alone, in us: score of 5 layers, arguments 102 and 128, copy command
-// 103 and 129 (with an event behind every call 106 and 129); select of one
-// layer 14.7 and 30.7, 16.6 and 32.3 (19.8 and 31.4); redundancy of 28 layers, copy
-// command 17.4 and 31.0, a kernel that reads the pinned table 18.1 and 31.6.
+// Copy the descriptor table to the device unless it is there. A call that runs
+// takes the last such call's table when they are equal (only append reads the
+// chunk fields; an append's own table serves calls on its stream).  Calls of a
+// context are ordered, so a slot may be written while the calls that read its
+// last table are still queued. A captured call never takes a table that lies
+// outside its graph, which later calls overwrite, nor leaves one to calls that
+// run, since a recorded copy has not: it takes the last one recorded into the
+// same capture on its stream, or records a copy whose values are kernel
+// arguments (in the graph, with no host memory to outlive it) into a slot of
+// the second half. Outside a capture up to kDescPerStore layers travel as
+// arguments, too; more by a copy command from pinned memory, one for any
+// number.  An event marks the end of that copy and nothing else: one behind
+// every call, without a system-scope fence, cost 2 us of the stream a call and
+// 3 us of a wait for it (which then needs a fence of its own).  A new table
+// every call, in a row and alone, in us: score of 5 layers, arguments 102 and
+// 128, copy command 103 and 129 (with an event behind every call 106 and 129);
+// select of one layer 14.7 and 30.7, 16.6 and 32.3 (19.8 and 31.4); redundancy
+// of 28 layers, copy command 17.4 and 31.0, a kernel that reads the pinned
+// table 18.1 and 31.6.
 omnimem_status upload(omnimem_ctx* ctx, const omnimem_layer* layers, hipStream_t st, const LayerDesc** dev,
                       const omnimem_chunk* chunks = nullptr) {
   const int L = ctx->cfg.n_layers;

@@ -75,15 +75,15 @@ struct Dims {
 // one workgroup per row, W = the number of rows, and a single segment.
 constexpr int kScoreBlock = 256;  // rows a workgroup keeps in registers
 constexpr int kScoreTile = 64;    // rows per streamed tile
-// Partials (of 256 rows) kept for a pass whose context has at most
-// `capacity` rows, and the segments a row may have in a call of `rows`
-// rows.  Four fill the chip from about 170 rows on; with fewer (a short chunk, few layers or heads)
-// they would leave slots without a workgroup, so a row may have as many as
-// the partials allow (at least 4096: 8 MB and 4 MB).  Four against this, the
-// score call: 28 heads of width 128, 128 queries, 4224 keys 53 -> 38 us;
-// 256 queries, 40256 keys 346 -> 197 us; 2 layers x 16 heads of fp32 width 64, 1024
-// queries, 4096 keys 206 -> 184 us; 1 layer x 28 heads, 2048 queries
-// (224 rows) as before.
+// Partials (of 256 rows) kept for a pass whose context has at most `capacity`
+// rows, and the segments a row may have in a call of `rows` rows.  Four fill
+// the chip from about 170 rows on; with fewer (a short chunk, few layers or
+// heads) they would leave slots without a workgroup, so a row may have as many
+// as the partials allow (at least 4096: 8 MB and 4 MB).  Four against this, the
+// score call: 28 heads of width 128, 128 queries, 4224 keys 53 -> 38 us; 256
+// queries, 40256 keys 346 -> 197 us; 2 layers x 16 heads of fp32 width 64, 1024
+// queries, 4096 keys 206 -> 184 us; 1 layer x 28 heads, 2048 queries (224 rows)
+// as before.
 constexpr int kMinSegs = 4, kRowSegs = 64, kMinPartials = 4096;
 __host__ __device__ inline int64_t plan_partials(int64_t capacity) {
   return capacity * kMinSegs > kMinPartials ? capacity * kMinSegs : kMinPartials;
@@ -418,8 +418,8 @@ __device__ inline void dma16_opaque(const void* g, void* lds) {
 
 // dma16_opaque with the global address split into a wave-uniform base (in
 // scalar registers) and a 32-bit per-lane byte offset, so that no 64-bit
-// address arithmetic runs per lane.  (vcc is named so that the saved M0 goes
-// to a numbered register.)
+// address arithmetic runs per lane.  (vcc is named so that the saved M0 goes to
+// a numbered register.)
 __device__ inline void dma16_opaque_s(const void* base, uint32_t off, void* lds) {
   const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane(
       (int)(uintptr_t)(__attribute__((address_space(3))) void*)lds);
@@ -449,24 +449,24 @@ __device__ inline void pin(V& v) { asm volatile("" : "+v"(v)); }
 
 
 // ---------------------------------------------------------------------------
-// fp32 products on the bf16 matrix cores.  An fp32 value x is the exact sum
-// of three bf16 values: x rounded to nearest, the rest rounded to nearest,
-// and what is left (at most 2^-8 and 2^-17 of the power of two at or below
-// |x|, of either sign).  A product of two values is nine bf16 products; six
-// of them are added in fp32 by the MFMA.  The three left out (a middle part
-// with a last part, twice, and the last parts) are together below 1.01 2^-24 of the
-// product of the two powers of two, of either sign: their sum over a row has
-// no bias.  (Parts cut off instead of rounded all have x's sign, and the same
-// three products take up to 2^-21 off every product.)  Six 32x32x16 bf16
-// MFMAs (32 cycles each) replace eight 32x32x2 fp32 ones (64 cycles each).
-// Error of a dot product of 128 terms over the norms, rms and largest of
-// 16384 against 64 bits, in 2^-24, the fp32 MFMA and this: N(0, 1) rows 0.31 and
-// 2.1, 0.10 and 1.0; a row with a near copy of itself 2.7 and 12.4, 1.1 and
-// 4.4; one channel a million times the others, the first one 4.8 and 22, 2.0
-// and 8.9, the last one 0.60 and 2.2, 1.08 and 5.5 (the one order where the
-// fp32 MFMA is the closer: it adds two products at a time, the bf16 MFMA cuts the smaller
-// ones of sixteen near the last place of the largest).
-// Rows are kept as [D leading | D middle | D last] bf16.
+// fp32 products on the bf16 matrix cores.  An fp32 value x is the exact sum of
+// three bf16 values: x rounded to nearest, the rest rounded to nearest, and
+// what is left (at most 2^-8 and 2^-17 of the power of two at or below |x|, of
+// either sign).  A product of two values is nine bf16 products; six of them are
+// added in fp32 by the MFMA.  The three left out (a middle part with a last
+// part, twice, and the last parts) are together below 1.01 2^-24 of the product
+// of the two powers of two, of either sign: their sum over a row has no bias.
+// (Parts cut off instead of rounded all have x's sign, and the same three
+// products take up to 2^-21 off every product.)  Six 32x32x16 bf16 MFMAs (32
+// cycles each) replace eight 32x32x2 fp32 ones (64 cycles each). Error of a dot
+// product of 128 terms over the norms, rms and largest of 16384 against 64
+// bits, in 2^-24, the fp32 MFMA and this: N(0, 1) rows 0.31 and 2.1, 0.10 and
+// 1.0; a row with a near copy of itself 2.7 and 12.4, 1.1 and 4.4; one channel
+// a million times the others, the first one 4.8 and 22, 2.0 and 8.9, the last
+// one 0.60 and 2.2, 1.08 and 5.5 (the one order where the fp32 MFMA is the
+// closer: it adds two products at a time, the bf16 MFMA cuts the smaller ones
+// of sixteen near the last place of the largest). Rows are kept as [D leading |
+// D middle | D last] bf16.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
@@ -493,10 +493,11 @@ __device__ inline void store_split(uint16_t* dst, int D, const uint4& v) {
 }
 
 // Whether the parts serve values (given as their bits): each 0, or of a
-// magnitude in [2^-50, 2^60).  Then the lowest bit of a product that counts stays above
-// the smallest normal number, and no rounded part or sum of 128 products passes the largest
-// one.  Blocks of rows with any other value (a product of an infinity with
-// another's zero part would be NaN) are multiplied as fp32 (mma_f32).
+// magnitude in [2^-50, 2^60).  Then the lowest bit of a product that counts
+// stays above the smallest normal number, and no rounded part or sum of 128
+// products passes the largest one.  Blocks of rows with any other value (a
+// product of an infinity with another's zero part would be NaN) are multiplied
+// as fp32 (mma_f32).
 struct SplitRange {
   uint32_t top = 0, low = ~0u;  // largest magnitude; smallest above 0, less 1 (0 counts as the largest word)
   __device__ inline void add(uint32_t u) {
@@ -579,8 +580,9 @@ struct SplitTile {  // an LDS stage of kScoreTile such rows
   }
   // One 32-row block of a stage against a register block.  The products with
   // a middle or last part of every k-step come first, while the sum is small
-  // (each is at most 2^-8 of its whole product, of either sign) and so are its roundings, then
-  // the leading parts' products; the leading fragments are read from LDS again for them.
+  // (each is at most 2^-8 of its whole product, of either sign) and so are
+  // its roundings, then the leading parts' products; the leading fragments
+  // are read from LDS again for them.
   __device__ static inline floatx16 mma(const uint16_t* lds, int r, int half, const bf16x8 (&b)[NKS][3]) {
     floatx16 acc = floatx16{};
 #pragma unroll

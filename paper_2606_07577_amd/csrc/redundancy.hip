@@ -81,19 +81,6 @@ __global__ __launch_bounds__(1024) void modality_lists(const LayerDesc* __restri
   if (threadIdx.x == 0) { counts[2 * l] = kv; counts[2 * l + 1] = N - kv; }
 }
 
-// 16 MFMAs: the 32-row block `row` of an LDS stage against two 32-column
-// blocks of register operands; each LDS fragment feeds two MFMAs.
-template <typename M, typename Tl, int NKS, typename T>
-__device__ inline void mma_block(floatx16 (&acc)[2], const T* lds, int row, int half,
-                                 const typename M::frag (&b)[2][NKS]) {
-#pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) {
-    const typename M::frag f = Tl::template frag<M>(lds, row, ks, half);
-    acc[0] = M::mma(f, b[0][ks], ks ? acc[0] : floatx16{});
-    acc[1] = M::mma(f, b[1][ks], ks ? acc[1] : floatx16{});
-  }
-}
-
 template <typename T, int D>
 struct GatherShape {
   static constexpr int LPR = D * (int)sizeof(T) / 16;  // lanes per row
@@ -115,9 +102,9 @@ constexpr int kListRows = 128;
 
 template <typename T, int D, bool PERM>
 __global__ __launch_bounds__(256) void lists_norms(const LayerDesc* __restrict__ layers, Dims dm, int on_keys,
-                                                   int* __restrict__ pos, int* __restrict__ counts, uint16_t* __restrict__ perm,
-                                                   uint8_t* __restrict__ odd, float* __restrict__ inv,
-                                                   int* __restrict__ best) {
+                                                   int* __restrict__ pos, int* __restrict__ counts,
+                                                   uint16_t* __restrict__ perm, uint8_t* __restrict__ odd,
+                                                   float* __restrict__ inv, int* __restrict__ best) {
   const int l = blockIdx.z, g = blockIdx.y;
   const LayerDesc Ld = layers[l];
   const int N = Ld.n;

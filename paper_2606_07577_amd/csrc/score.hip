@@ -12,9 +12,10 @@
 //                query, then per (head, key): sum_i exp(S[i][j] - lse[i])
 //   head_sum     a[g][j] = sum over the G query heads of KV head g.
 // Scores stay in registers; nothing of size queries x keys touches HBM.
-// Both passes stream one operand through double-buffered LDS (next tile
-// prefetched into registers while the current one is consumed) and keep
-// the other in registers, 64 rows per wavefront.  lse_merge joins them.
+// Both passes stream one operand through double-buffered LDS (the next tile
+// copied there while the current one is consumed) and keep the other in
+// registers, 64 rows per wavefront (fp32, see SplitTile: 32).  lse_merge
+// joins them.
 #include "common.h"
 
 namespace omnimem {
@@ -84,7 +85,8 @@ __device__ inline void online_update(const floatx16& acc, float sl2, float& m, f
 }
 
 
-// fp32 rows as three-part bf16 rows (SplitTile), written by split_rows (null: there are none, see Workspace).
+// fp32 rows as three-part bf16 rows (SplitTile), written by split_rows (null:
+// there are none, see Workspace).
 struct SplitRows {
   const uint16_t* q;  // [L][Hq][max_chunk][3 D]
   const uint16_t* k;  // [L][Hkv][max_tokens][3 D]
@@ -319,16 +321,17 @@ __device__ inline void lse_segment(const LayerDesc& Ld, const Dims& dm, int, int
   }
 }
 
-// The same for fp32 rows, as three-part products (SplitTile): eight
-// wavefronts keep 32 queries each; per tile, the MFMAs of both 32-key blocks,
-// then their exponentials under a running maximum (the largest terms' exponents
-// near 0, where they round least).  Bound by the MFMAs, six per k-step of
-// 16.  2 layers x 16 heads, 1024 queries, 3072 + 1024 keys of width 64: 104 us
-// (234 us with the 32x32x2 fp32 MFMA), the column sums 86 us (174 us); one
-// layer x 28 heads, 1500 queries, 4500 keys of width 128: 243 us (516 us, with
-// 123 registers spilled) and 242 us (504 us).  A segment with a value that the parts do not serve
-// is done again as fp32, from the rows themselves (the flags are asked for at its start and
-// looked at when its tiles are done, so that no ordinary segment waits for them).
+// The same for fp32 rows, as three-part products (SplitTile): eight wavefronts
+// keep 32 queries each; per tile, the MFMAs of both 32-key blocks, then their
+// exponentials under a running maximum (the largest terms' exponents near 0,
+// where they round least).  Bound by the MFMAs, six per k-step of 16.  2 layers
+// x 16 heads, 1024 queries, 3072 + 1024 keys of width 64: 82 us (234 us with
+// the 32x32x2 fp32 MFMA), the column sums 87 us (174 us); one layer x 28 heads,
+// 1500 queries, 4500 keys of width 128: 204 us (516 us, with 123 registers
+// spilled) and 224 us (504 us).  A segment with a value that the parts do not
+// serve is done again as fp32, from the rows themselves (the flags are asked
+// for at its start and looked at when its tiles are done, so that no ordinary
+// segment waits for them).
 template <int D>
 __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int l, int h, int q0, int kr0, int kr1,
                                        int64_t pslot, uint16_t* kt0, uint16_t* kt1, const SplitRows& sr,
@@ -405,9 +408,8 @@ __device__ inline void lse_segment_f32(const LayerDesc& Ld, const Dims& dm, int 
 // interval row by row.  Consecutive workgroups share rows and heads, so
 // their logical ids go to one XCD's L2.
 template <typename T, int D>
-__global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_SIMD)) void lse_pass(const LayerDesc* __restrict__ layers, Dims dm,
-                                                                          PassPlan pl, SplitRows sr,
-                                                                          float2* __restrict__ part) {
+__global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_SIMD)) void lse_pass(
+    const LayerDesc* __restrict__ layers, Dims dm, PassPlan pl, SplitRows sr, float2* __restrict__ part) {
   using Sh = PassShape<T, D>;
   __shared__ __attribute__((aligned(256))) uint16_t kt0[Sh::ELEMS];
   __shared__ __attribute__((aligned(256))) uint16_t kt1[Sh::ELEMS];
@@ -825,10 +827,9 @@ __device__ inline void colsum_segment_f32(const LayerDesc& Ld, const Dims& dm, i
 // Pass 2 over the plan's tiles (rows = (layer, head, 256-key block), tiles
 // = the 64-query tiles that see a key of the block), walked like lse_pass.
 template <typename T, int D>
-__global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_SIMD)) void colsum_pass(const LayerDesc* __restrict__ layers, Dims dm,
-                                                                             PassPlan pl, SplitRows sr,
-                                                                             const float* __restrict__ lse2_all,
-                                                                             float* __restrict__ part) {
+__global__ __launch_bounds__((PassShape<T, D>::THREADS), (PassShape<T, D>::PER_SIMD)) void colsum_pass(
+    const LayerDesc* __restrict__ layers, Dims dm, PassPlan pl, SplitRows sr, const float* __restrict__ lse2_all,
+    float* __restrict__ part) {
   using Sh = PassShape<T, D>;
   __shared__ __attribute__((aligned(256))) uint16_t qt0[Sh::ELEMS];
   __shared__ __attribute__((aligned(256))) uint16_t qt1[Sh::ELEMS];
@@ -906,7 +907,8 @@ __global__ void head_sum(const LayerDesc* __restrict__ layers, Dims dm, PassPlan
     int64_t start = Ld.cs_base;
     for (int bb = 0; bb < b; ++bb) start += cs_row_tiles(Ld.n, Ld.n_cache, Ld.n_chunk, bb, dm.causal);
     // the segment partials of up to kHeadsAtOnce query heads requested at
-    // once, then added in head and segment order
+    // once, then added: four segments of every one of the heads, head by
+    // head, then the next four
     constexpr int kHeadsAtOnce = 8;
     for (int h0 = 0; h0 < dm.G; h0 += kHeadsAtOnce) {
       int nseg[kHeadsAtOnce], most = 0;
@@ -938,9 +940,10 @@ __global__ void head_sum(const LayerDesc* __restrict__ layers, Dims dm, PassPlan
 
 // fp32 queries and keys of every layer as three-part rows: four elements per
 // thread; and the workgroup's flag.  Grid: (H_q x q_blocks, the query heads'
-// workgroups, then H_kv x k_blocks; L): as many as the call's longest chunk and working set have
-// blocks, not the context's capacity (4 layers x (28 + 4) heads, 500 + 200 rows in
-// a context of 40960 rows: a score call 167 -> 128 us).
+// workgroups, then H_kv x k_blocks; L): as many as the call's longest chunk and
+// working set have blocks, not the context's capacity (4 layers x (28 + 4)
+// heads, 500 + 200 rows in a context of 40960 rows: a score call 167 -> 128
+// us).
 template <int D>
 __global__ __launch_bounds__(256) void split_rows(const LayerDesc* __restrict__ layers, Dims dm, int q_blocks,
                                                   int k_blocks, uint16_t* __restrict__ sq, uint16_t* __restrict__ sk,
@@ -989,8 +992,8 @@ void launch_typed(const Dims& dm, const LayerDesc* desc, const Workspace& ws, co
     const int qb = (lp.longest + kSplitRows - 1) / kSplitRows, kb = (cp.longest + kSplitRows - 1) / kSplitRows;
     if (sr.q)
       OMNIMEM_LAUNCH(ws, K_SPLIT, st,
-                     split_rows<D><<<dim3(dm.Hq * qb + dm.Hkv * kb, dm.L), 256, 0, st>>>(desc, dm, qb, kb, ws.split_q, ws.split_kv,
-                                                                                  ws.odd_q, ws.odd_kv));
+                     split_rows<D><<<dim3(dm.Hq * qb + dm.Hkv * kb, dm.L), 256, 0, st>>>(
+                         desc, dm, qb, kb, ws.split_q, ws.split_kv, ws.odd_q, ws.odd_kv));
   }
   if (lp.W > 0)
     OMNIMEM_LAUNCH(ws, K_LSE, st, lse_pass<T, D><<<lp.P, kTh, 0, st>>>(desc, dm, lp, sr, ws.lse_part));
@@ -1002,16 +1005,16 @@ void launch_typed(const Dims& dm, const LayerDesc* desc, const Workspace& ws, co
   OMNIMEM_LAUNCH(ws, K_HEADSUM, st, head_sum<<<g3, 256, 0, st>>>(desc, dm, cp, ws.part, a));
 }
 
-// Plan a pass of W tiles in `rows` rows, the longest of t_max tiles.  With
-// rows to spare (at least 8 per workgroup slot) the hardware dispatcher
-// balances one workgroup per row best.  Otherwise chunks hold at least
-// t_max / (segs - 1) tiles (segs: the segments a row may have) and, if the
-// work allows, about two rows (a segment's start costs about as much as a
-// few tiles); then as many rounds of P chunks as fit, with the chunk size
-// that fills the rounds evenly.  Work below a chunk of one tile per slot is
-// not kept together: chunks of at least two or four tiles were slower wherever they
-// left slots idle (8 heads, 400 + 200 rows: 21.4, 27.9 and 37.1 us with one, two
-// and four) and no faster elsewhere.
+// Plan a pass of W tiles in `rows` rows, the longest of t_max tiles.  With rows
+// to spare (at least 8 per workgroup slot) the hardware dispatcher balances one
+// workgroup per row best.  Otherwise chunks hold at least t_max / (segs - 1)
+// tiles (segs: the segments a row may have) and, if the work allows, about two
+// rows (a segment's start costs about as much as a few tiles); then as many
+// rounds of P chunks as fit, with the chunk size that fills the rounds evenly.
+// Work below a chunk of one tile per slot is not kept together: chunks of at
+// least two or four tiles were slower wherever they left slots idle (8 heads,
+// 400 + 200 rows: 21.4, 27.9 and 37.1 us with one, two and four) and no faster
+// elsewhere.
 PassPlan choose_plan(int64_t W, int64_t rows, int t_max, int segs, int max_workgroups) {
   PassPlan p{W, 0, 1, segs, 0};
   if (W <= 0) return p;

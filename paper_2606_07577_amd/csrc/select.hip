@@ -1327,20 +1327,20 @@ struct RowCopy {
   static constexpr int EPC = 16 / (int)sizeof(T);
 };
 
-constexpr int kStageGroups = 1024;   // workgroups of a staging launch, about
+constexpr int kStageGroups = 1024;   // about the workgroups of a staging launch
 
 // Zero the read flags and ticket counters, and stage the slots that take a
-// row in front of them.  Grid: (tiles, H_kv, L);
-// workgroup x stages the kGatherRows audio slots from M_v + kGatherRows x,
-// then every gridDim.x-th tile behind, up to the end of the run (the
-// run that moves back is a prefix of the audio slots, so it lies in the
-// first stage_rows of them unless it is too long), and zeroes every
-// gridDim.x-th read flag.  Most tiles lie behind the run, so a workgroup for each
-// would be mostly launch: about kStageGroups share them, which still has every
-// compute unit copy.  A tile's rows are all requested before the first is stored.
-// 28 layers x 4 heads, a reserve of 6144 rows: the select call 141.8 -> 137.7 us.  The workgroup of tile 0 also checks the first
-// slot past the staging rows; if that one moves back too, it counts the
-// whole run (the shortfall) for the status word.
+// row in front of them.  Grid: (tiles, H_kv, L); workgroup x stages the
+// kGatherRows audio slots from M_v + kGatherRows x, then every gridDim.x-th
+// tile behind, up to the end of the run (the run that moves back is a prefix
+// of the audio slots, so it lies in the first stage_rows of them unless it
+// is too long), and zeroes every gridDim.x-th read flag.  The workgroup of
+// tile 0 also checks the first slot past the staging rows; if that one moves
+// back too, it counts the whole run (the shortfall) for the status word.
+// Most tiles lie behind the run, so a workgroup for each would be mostly
+// launch: about kStageGroups share them, which still has every compute unit
+// copy.  A tile's rows are all requested before the first is stored.  28
+// layers x 4 heads, a reserve of 6144 rows: the select call 141.8 -> 137.7 us.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void stage_moved_back(const LayerDesc* __restrict__ layers, Dims dm,
                                                         const int32_t* __restrict__ idx, const int* __restrict__ eff,

@@ -1,11 +1,12 @@
 """fp32 inputs: products on the matrix cores from three bf16 parts per value.
 
 Working sets around the tile and block edges of the score and Gram passes
-(32-row register blocks, 64-row tiles, 256-row workgroups), and rows whose
-scales differ by many powers of two (the parts are exact at any scale), against
-the float64 oracle.  An fp32 sum of d products carries about sqrt(d) / 2
-roundings of 2^-24 of its size, under 6e-7 at d = 128 relative to the norms;
-the importance adds the exponential's and the sum's own roundings.
+(32-row register blocks, 64-row tiles, 256-row workgroups), and rows of
+scales from 2^-39 to 2^30, against the float64 oracle (what the parts lose or
+cannot hold: test_gpu_fp32_bias.py, test_gpu_fp32_range.py).  An fp32 sum of d products carries about sqrt(d) / 2
+roundings of 2^-24 of its size, and the part products left out less than one,
+under 6e-7 at d = 128 relative to the norms; the importance adds the
+exponential's and the sum's own roundings.
 """
 import numpy as np
 import pytest

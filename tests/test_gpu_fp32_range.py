@@ -102,3 +102,28 @@ def test_redundancy_of_extreme_rows(kind, n, source, d):
     assert (got[:, n:] == 7.0).all()
     assert np.abs(got[0, :n][keep] - ref[0][keep]).max() <= 6e-7
     assert np.abs(got[1, :n] - ref[1]).max() <= 6e-7
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_redundancy_of_many_heads(d):
+    # 9 layers x 2 heads (the work dealt to the eight XCDs); a tiny row, an infinity and a NaN in some of them
+    rng = np.random.default_rng(d)
+    layers, n = 9, 300
+    x = rng.standard_normal((layers, 2, n, d), dtype=np.float32)
+    x[:, :, 250] = x[:, :, 3] + np.float32(0.01) * x[:, :, 250]
+    mod = (np.arange(n) % 4 == 3).astype(np.uint8)
+    refs = [orc.redundancy(x[l].astype(np.float64), mod, "max") for l in range(layers)]
+    x[2, 1, 100] *= np.float32(2.0**-70)
+    x[4, 0, 7, 0], x[7, 1, 8, 1] = np.inf, np.nan
+    keep = np.ones((layers, 2, n), bool)
+    keep[4, 0, 7], keep[7, 1, 8] = False, False
+    for l, g in ((4, 0), (7, 1)):
+        rows = keep[l, g]
+        refs[l][g, rows] = orc.redundancy(x[l, g, rows][None].astype(np.float64), mod[rows], "max")[0]
+    t, m = torch.from_numpy(x).cuda(), torch.from_numpy(mod).cuda()
+    ctx = om.Context(layers, 4, 2, d, n, n, dtype=om.F32)
+    s = torch.zeros(layers, 2, n, device="cuda")
+    ctx.omnimem_redundancy([om.make_layer(None, t[l], t[l], m, 0) for l in range(layers)], s)
+    got = s.double().cpu().numpy()
+    ctx.close()
+    assert np.abs(got - np.stack(refs))[keep].max() <= 6e-7
