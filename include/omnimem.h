@@ -157,8 +157,8 @@ void omnimem_config_default(omnimem_config* cfg);
 /* Create a context on the current HIP device.  Allocates every workspace
  * buffer for cfg's capacities.  The larger ones: the score passes' partial
  * sums, 8 KiB for every query head and 256 rows of max_chunk and 4 KiB for
- * every query head and 256 rows of max_tokens (at least 8 and 4 MiB in
- * all); and with fp32 6 bytes per element of the queries and of one of the
+ * every query head and 256 rows of max_tokens (8 and 4 MiB in all where
+ * that is less, or what a small context can use of it); and with fp32 6 bytes per element of the queries and of one of the
  * caches ([L][H_q][max_chunk][d] and [L][H_kv][max_tokens][d]).  The fp32
  * ones are left out if there is no memory for them: scores and redundancy
  * then take the fp32 matrix instructions on the rows as they are, with the

@@ -564,9 +564,9 @@ omnimem_status omnimem_create(const omnimem_config* cfg, omnimem_ctx** out) {
   ws.stage_rows = c.inplace_stage_rows;
   const size_t elt = c.dtype == OMNIMEM_BF16 ? 2 : 4;
   if ((e = dalloc(ctx, &ws.desc, (size_t)2 * kSlots * L)) != hipSuccess ||
-      (e = dalloc(ctx, &ws.lse_part, (size_t)plan_partials((int64_t)(L * Hq) * dm.qb) * kScoreBlock)) != hipSuccess ||
+      (e = dalloc(ctx, &ws.lse_part, (size_t)plan_partials((int64_t)(L * Hq) * dm.qb, T) * kScoreBlock)) != hipSuccess ||
       (e = dalloc(ctx, &ws.lse2, L * Hq * Cm)) != hipSuccess ||
-      (e = dalloc(ctx, &ws.part, (size_t)plan_partials((int64_t)(L * Hq) * dm.kb) * kScoreBlock)) != hipSuccess ||
+      (e = dalloc(ctx, &ws.part, (size_t)plan_partials((int64_t)(L * Hq) * dm.kb, Cm) * kScoreBlock)) != hipSuccess ||
       (e = dalloc(ctx, &ws.pos, L * 2 * (size_t)list_stride(T))) != hipSuccess ||
       (e = dalloc(ctx, &ws.counts, L * 2)) != hipSuccess ||
       (e = dalloc(ctx, &ws.inv_norm, L * Hkv * T)) != hipSuccess ||

@@ -76,20 +76,22 @@ struct Dims {
 constexpr int kScoreBlock = 256;  // rows a workgroup keeps in registers
 constexpr int kScoreTile = 64;    // rows per streamed tile
 // Partials (of 256 rows) kept for a pass whose context has at most `capacity`
-// rows, and the segments a row may have in a call of `rows` rows.  Four fill
-// the chip from about 170 rows on; with fewer (a short chunk, few layers or
-// heads) they would leave slots without a workgroup, so a row may have as many
-// as the partials allow (at least 4096: 8 MB and 4 MB).  Four against this, the
-// score call: 28 heads of width 128, 128 queries, 4224 keys 53 -> 38 us; 256
-// queries, 40256 keys 346 -> 197 us; 2 layers x 16 heads of fp32 width 64, 1024
-// queries, 4096 keys 206 -> 184 us; 1 layer x 28 heads, 2048 queries (224 rows)
-// as before.
+// rows, each streaming at most `streamed` rows, and the segments a row may have
+// in a call of `rows` rows.  Four fill the chip from about 170 rows on; with
+// fewer (a short chunk, few layers or heads) they would leave slots without a
+// workgroup, so a row may have as many as the partials allow: at least 4096 (8
+// MB and 4 MB), or one per tile and one more where that is less, which is all
+// that a plan can use.  Four against this, the score call: 28 heads of width
+// 128, 128 queries, 4224 keys 53 -> 38 us; 256 queries, 40256 keys 346 -> 197
+// us; 2 layers x 16 heads of fp32 width 64, 1024 queries, 4096 keys 206 -> 184
+// us; 1 layer x 28 heads, 2048 queries (224 rows) as before.
 constexpr int kMinSegs = 4, kRowSegs = 64, kMinPartials = 4096;
-__host__ __device__ inline int64_t plan_partials(int64_t capacity) {
-  return capacity * kMinSegs > kMinPartials ? capacity * kMinSegs : kMinPartials;
+inline int64_t plan_partials(int64_t capacity, int64_t streamed) {
+  const int64_t tiles = (streamed + kScoreTile - 1) / kScoreTile;
+  return std::max(capacity * kMinSegs, std::min<int64_t>(kMinPartials, capacity * (tiles + 1)));
 }
-inline int plan_segs(int64_t capacity, int64_t rows) {
-  return (int)std::min<int64_t>(kRowSegs, plan_partials(capacity) / std::max<int64_t>(rows, 1));
+inline int plan_segs(int64_t capacity, int64_t streamed, int64_t rows) {
+  return (int)std::min<int64_t>(kRowSegs, plan_partials(capacity, streamed) / std::max<int64_t>(rows, 1));
 }
 constexpr int kGatherRows = 64;   // slots per tile (and workgroup) of the in-place gather and its staging
 struct PassPlan {

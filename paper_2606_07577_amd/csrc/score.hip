@@ -1075,8 +1075,10 @@ void plan_score(const Dims& dm, LayerDesc* layers, int max_workgroups, PassPlan*
     cs_w += (int64_t)dm.Hq * ch;
     cs_rows += ch > 0 ? (int64_t)dm.Hq * nb : 0;
   }
-  *lse_plan = choose_plan(lse_w, lse_rows, lse_tmax, plan_segs((int64_t)dm.L * dm.Hq * dm.qb, lse_rows), max_workgroups);
-  *cs_plan = choose_plan(cs_w, cs_rows, cs_tmax, plan_segs((int64_t)dm.L * dm.Hq * dm.kb, cs_rows), max_workgroups);
+  *lse_plan = choose_plan(lse_w, lse_rows, lse_tmax,
+                          plan_segs((int64_t)dm.L * dm.Hq * dm.qb, dm.max_tokens, lse_rows), max_workgroups);
+  *cs_plan = choose_plan(cs_w, cs_rows, cs_tmax,
+                         plan_segs((int64_t)dm.L * dm.Hq * dm.kb, dm.max_chunk, cs_rows), max_workgroups);
   lse_plan->longest = chunk;
   cs_plan->longest = rows;
 }
