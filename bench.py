@@ -42,37 +42,37 @@ KERNEL_SOURCES = ["include/omnimem.h"] + [f"paper_2606_07577_amd/csrc/{f}" for f
     "common.h", "api.hip", "score.hip", "redundancy.hip", "allocate.hip", "select.hip")]
 MEASURED_TRAFFIC = {
     "qwen7b-stream-64x28": {
-        "sources_sha256": "24c825019fb7279f0410ec26c325d4a26aea536854ca8f7aa8afde88e6a5ded8",
-        "append_chunk": 235384164, "lse_pass": 604350999, "lse_merge": 19381020, "colsum_pass": 622659771,
-        "head_sum": 21864299, "lists_norms": 181314004, "gram_sym": 816413190, "gram_finish": 6206188,
-        "avba_partials": 6072666, "avba_allocate": 181106, "psi_topk_reg": 20871092,
-        "stage_moved_back": 15224527, "gather_inplace": 417904305,
+        "sources_sha256": "ff1c5ceebacea382ea8efba5b83fd77a8da6882745e1c3c441d8a49665989eba",
+        "append_chunk": 235376863, "lse_pass": 604439429, "lse_merge": 19397884, "colsum_pass": 622717447,
+        "head_sum": 21882584, "lists_norms": 180643788, "gram_sym": 1101864611, "gram_finish": 6198013,
+        "avba_partials": 6072681, "avba_allocate": 181106, "psi_topk_reg": 20871133, "stage_moved_back":
+        14538551, "gather_inplace": 417913442,
     },
     "qwen7b-28layer-6144": {
-        "sources_sha256": "24c825019fb7279f0410ec26c325d4a26aea536854ca8f7aa8afde88e6a5ded8",
-        "lse_pass": 608507806, "lse_merge": 19381186, "colsum_pass": 613571541, "head_sum": 22237014,
-        "lists_norms": 184685541, "gram_sym": 823118569, "gram_finish": 6248350, "avba_partials": 6110176,
-        "avba_allocate": 123965, "psi_topk_reg": 14505207, "gather_compact": 471744325,
+        "sources_sha256": "ff1c5ceebacea382ea8efba5b83fd77a8da6882745e1c3c441d8a49665989eba",
+        "lse_pass": 608291091, "lse_merge": 19398443, "colsum_pass": 613611359, "head_sum": 22256293,
+        "lists_norms": 183997360, "gram_sym": 1286489899, "gram_finish": 6240230, "avba_partials": 6110192,
+        "avba_allocate": 123965, "psi_topk_reg": 14505263, "gather_compact": 471744243,
     },
     "qwen7b-layer-6144": {
-        "sources_sha256": "24c825019fb7279f0410ec26c325d4a26aea536854ca8f7aa8afde88e6a5ded8",
-        "lse_pass": 31056374, "lse_merge": 1738778, "colsum_pass": 33076993, "head_sum": 1460231,
-        "lists_norms": 6721705, "gram_sym": 14042062, "gram_finish": 245756, "avba_partials": 331903,
-        "avba_allocate": 36191, "psi_topk_reg": 697023, "gather_compact": 16881639,
+        "sources_sha256": "ff1c5ceebacea382ea8efba5b83fd77a8da6882745e1c3c441d8a49665989eba",
+        "lse_pass": 31129108, "lse_merge": 1744926, "colsum_pass": 33006360, "head_sum": 1468447,
+        "lists_norms": 6695121, "gram_sym": 13442925, "gram_finish": 237564, "avba_partials": 331904,
+        "avba_allocate": 36191, "psi_topk_reg": 697071, "gather_compact": 16881687,
     },
     "qwen7b-layer-6144-hidden": {
-        "sources_sha256": "24c825019fb7279f0410ec26c325d4a26aea536854ca8f7aa8afde88e6a5ded8",
-        "lse_pass": 31055225, "lse_merge": 1738710, "colsum_pass": 33082548, "head_sum": 1460345,
-        "modality_lists": 65832, "hidden_norms": 44175417, "gram_wide": 188173558, "hidden_finish": 138239,
-        "avba_partials": 331903, "avba_allocate": 36191, "layer_inputs": 272514, "psi_topk_reg": 227003,
-        "gather_compact": 16881708, "gather_hidden": 58879398,
+        "sources_sha256": "ff1c5ceebacea382ea8efba5b83fd77a8da6882745e1c3c441d8a49665989eba",
+        "lse_pass": 31120239, "lse_merge": 1744858, "colsum_pass": 32928009, "head_sum": 1468526,
+        "modality_lists": 40104, "hidden_norms": 44175472, "gram_wide": 188153184, "hidden_finish": 147455,
+        "avba_partials": 331904, "avba_allocate": 36191, "layer_inputs": 272515, "psi_topk_reg": 227004,
+        "gather_compact": 16881798, "gather_hidden": 58879632,
     },
     "qwen7b-longcache-40960": {
-        "sources_sha256": "24c825019fb7279f0410ec26c325d4a26aea536854ca8f7aa8afde88e6a5ded8",
-        "lse_pass": 5085468639, "lse_merge": 3850240, "colsum_pass": 380252009, "head_sum": 5419069,
-        "lists_norms": 44044125, "gram_sym": 947909492, "gram_finish": 1499112, "avba_partials": 1492173,
-        "avba_allocate": 53599, "topk_hist": 2205441, "topk_bin": 1948912, "topk_emit": 2727622,
-        "gather_compact": 134783809,
+        "sources_sha256": "ff1c5ceebacea382ea8efba5b83fd77a8da6882745e1c3c441d8a49665989eba",
+        "lse_pass": 5083065277, "lse_merge": 3856391, "colsum_pass": 380420322, "head_sum": 5430417,
+        "lists_norms": 43878303, "gram_sym": 931033359, "gram_finish": 1490923, "avba_partials": 1492176,
+        "avba_allocate": 53599, "topk_hist": 2205445, "topk_bin": 1948970, "topk_emit": 2727627,
+        "gather_compact": 134782911,
     },
 }
 
